@@ -119,9 +119,9 @@ def load_traffic(kernel_key, src, workload):
 COPY_BYTES = 256 << 20
 COPY_KERNEL = "neg_kernel"  # the calibration copy: out = -in over COPY_BYTES of fp32
 KERNEL_KEYS = {"draft": "attn_bf16<128, false", "verify": "attn_bf16<128, true",
-               "accept": "argmax_partial<true, true>", "tree_scan": "tree_scan<true>",
+               "accept": "argmax_partial<true>", "tree_scan": "tree_scan<true>",
                "tree_rank": "tree_rank<true>", "tree_enum": "tree_enum",
-               "sample": "sample_partial<true, true>"}
+               "sample": "sample_partial<true>"}
 KERNEL_SRC = {"draft": "attn_bf16.hip", "verify": "attn_bf16.hip", "accept": "accept.hip",
               "tree_scan": "tree.hip", "tree_rank": "tree.hip", "tree_enum": "tree.hip",
               "sample": "accept.hip"}
@@ -372,7 +372,7 @@ def measure_sample(args, w, sets, G, torch, np, stream):
     nbytes = tokens * 2
     acc = outs[0]["accept_len"].cpu().numpy()
     ops = tokens * SAMPLE_OPS_PER_TOKEN
-    return {"us": round(us, 2), "kernel": "sample_partial<true,true>",
+    return {"us": round(us, 2), "kernel": "sample_partial<true>",
             "input": f"verified logits {w.batch} x {w.n_tree} x {w.vocab} bf16, T = 1",
             "gtokens_per_s": round(tokens / us / 1e3, 1), "gbps": round(nbytes / us / 1e3, 1),
             "hbm_frac": round(nbytes / us / 1e3 / HBM_PEAK_GBS, 4), "bound": "alu",

@@ -182,8 +182,8 @@ glance_status glance_greedy_accept(int32_t batch, int32_t n_nodes, int32_t vocab
  * root):
  *   root_entropy device [batch] float32, not NULL: the entropy (nats) of the
  *               softmax of row 0 of each sequence.  Computed in the same
- *               launch (fp32 sums relative to each chunk's maximum; the root
- *               row's workgroups read their chunk a second time); -inf logits
+ *               launch (fp32 sums, by workgroups of their own that read the
+ *               root rows a second time); -inf logits
  *               carry probability 0; undefined if row 0 holds a NaN or +inf.
  * All other arguments, outputs and the workspace as for glance_greedy_accept.
  */

@@ -4,11 +4,18 @@
 // argmax_partial  grid (row, vocabulary chunk): each workgroup streams one
 //                 chunk of one row with 16-byte loads and reduces it to a
 //                 packed (order key, ~index) word, so that the maximum word
-//                 is the largest value at the lowest index.
+//                 is the largest value at the lowest index.  With the root
+//                 entropy asked for, the first workgroups compute it.
 // accept_walk     one wave per sequence: lane v merges the chunk words of row
 //                 v, then the wave walks the tree from the root, finding the
 //                 child that carries the current row's argmax token with one
 //                 ballot per step.
+//
+// Rows of any vocabulary take the same vector loads: a row whose length is no
+// multiple of 16 bytes only makes them unaligned, which the memory pipeline
+// serves (at most one more cache line per wave-wide load); the values past a
+// row's last whole vector are loaded one by one.  2 x 33 x 50257 bf16, with
+// entropy: 13.6 us with one load per value, 7.6 us with these.
 //
 // sample_partial  the sampling walk's row draws (temperature T > 0): the same
 //                 grid and packed reduction as argmax_partial over
@@ -25,10 +32,10 @@
 //
 // Root entropy (optional): the target's next-token entropy at the round root,
 // H = -sum_w p(w) log p(w) over row 0 of each sequence (the scalar of the
-// paper's entropy law, Sec. 4).  The argmax workgroups of row 0 re-read their
-// chunk (1/n_nodes of the logits) to accumulate, relative to the chunk
-// maximum m found by the argmax, S = sum e^(z - m) and T = sum e^(z - m) (z - m);
-// the walk merges the chunks to H = log S - T / S.
+// paper's entropy law, Sec. 4).  Workgroups of their own, the first of the
+// grid, read a chunk of a root row once each and leave, relative to its
+// maximum m, S = sum e^(z - m) and T = sum e^(z - m) (z - m); the walk merges
+// them to H = log S - T / S.
 //
 // Order key of a float (fp32 bits, or bf16 bits shifted up 16): the sign-
 // magnitude encoding mapped to two's complement, so +0 and -0 both map to 0
@@ -40,6 +47,7 @@ namespace glance {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef u32x4 u32x4_any __attribute__((aligned(2)));  // at any bf16 or fp32 element
 
 __device__ __forceinline__ int order_key(unsigned int bits) {
   const int neg = (int)(0x80000000u - bits);  // -(magnitude) for a negative value
@@ -80,7 +88,7 @@ __device__ __forceinline__ float as_f32(unsigned u) { return __builtin_bit_cast(
 __device__ __forceinline__ float fmaximum(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 __device__ __forceinline__ float fmaximum3(float a, float b, float c) { return fmaximum(fmaximum(a, b), c); }
 
-// bf16 rows with 16-byte alignment.  A 32-bit word w holds two bf16 values:
+// bf16 rows, whole vectors of 8 values.  A 32-bit word w holds two bf16 values:
 // the high one read as fp32 is w itself (the low value only adds mantissa
 // bits below the bf16 precision, so the order of distinct bf16 values is
 // kept), the low one is w << 16.  Per 8 values the thread takes one fp32
@@ -104,7 +112,7 @@ __device__ __forceinline__ void argmax_bf16_fast(const unsigned short* x, int c0
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int e = e0 + u * 8 * 256;
-      v[u] = e < c1 ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + e))
+      v[u] = e < c1 ? (u32x4)__builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(x + e))
                     : u32x4{kPad, kPad, kPad, kPad};
     }
 #pragma unroll
@@ -136,97 +144,148 @@ __device__ __forceinline__ void argmax_bf16_fast(const unsigned short* x, int c0
   best_key = order_key(bits << 16);
 }
 
-template <bool BF16, bool VEC>
-__global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
-  __shared__ unsigned long long red[4];
-  const int chunk = blockIdx.x % p.chunks;
-  const long row = blockIdx.x / p.chunks;
-  const int c0 = chunk * p.chunk_len;
-  const int c1 = min(p.vocab, c0 + p.chunk_len);
+// (S, T) relative to maximum m, moved to the maximum M >= m:
+// e^(z-M) (z-M) = e^(m-M) e^(z-m) ((z-m) + (m-M)).
+__device__ __forceinline__ void entropy_rebase(float m, float M, float& S, float& T) {
+  if (S == 0.f) return;  // no mass yet (m may be -inf)
+  const float f = __builtin_amdgcn_exp2f((m - M) * 1.4426950408889634f);
+  T = (T + (m - M) * S) * f;
+  S *= f;
+}
+
+// Entropy statistics of values [chunk ent_len, +ent_len) of a sequence's row
+// 0: kEntropyStep values at a time in registers, their maximum first, then
+// both sums, each thread relative to its own running maximum.  Bound by the
+// load and 32 exponentials a thread and step, within the time the other
+// workgroups stream their chunks.  The whole acceptance at 4 x 64 x 152064
+// bf16: 54.8 us when the root rows' own argmax workgroups (8 of 512) read
+// their chunks a second time value by value, 17.5 us with these (76 more).
+template <bool BF16>
+__device__ __forceinline__ void entropy_chunk(const AcceptParams& p, int b, int chunk) {
+  constexpr int V = BF16 ? 8 : 4;  // values per 16-byte load
+  constexpr int LOADS = kEntropyStep / (256 * V);
+  __shared__ float red_m[4], red_s[4], red_t[4];
   const int tid = threadIdx.x;
-  int best_key = (int)0x80000000;
-  int best_idx = 0x7fffffff;
-  if (BF16) {
-    const unsigned short* x = static_cast<const unsigned short*>(p.logits) + row * (long)p.vocab;
-    if (VEC) {
-      argmax_bf16_fast(x, c0, c1, tid, best_key, best_idx);
-    } else {
-      for (int e = c0 + tid; e < c1; e += 256) {
-        const int k = order_key((unsigned int)x[e] << 16);
-        if (k > best_key) { best_key = k; best_idx = e; }
-      }
+  const char* rowp = static_cast<const char*>(p.logits) + (size_t)b * p.n_nodes * p.vocab * (BF16 ? 2 : 4);
+  const int begin = chunk * p.ent_len;
+  const int end = min(p.vocab, begin + p.ent_len);
+  float m = -__builtin_inff(), S = 0.f, T = 0.f;
+  for (int c0 = begin; c0 < end; c0 += kEntropyStep) {
+    const int c1 = min(end, c0 + kEntropyStep);
+    u32x4 w[LOADS];
+#pragma unroll
+    for (int l = 0; l < LOADS; ++l) {
+      const int e = c0 + (l * 256 + tid) * V;
+      w[l] = BF16 ? u32x4{0xff80ff80u, 0xff80ff80u, 0xff80ff80u, 0xff80ff80u}
+                  : u32x4{0xff800000u, 0xff800000u, 0xff800000u, 0xff800000u};  // -inf
+      if (e + V <= c1) w[l] = *reinterpret_cast<const u32x4_any*>(rowp + (size_t)e * (BF16 ? 2 : 4));
     }
-  } else {
-    const unsigned int* x = static_cast<const unsigned int*>(p.logits) + row * (long)p.vocab;
-    if (VEC) {
-      constexpr int kUnroll = 4;
-      for (int e0 = c0 + 4 * tid; e0 < c1; e0 += 4 * 256 * kUnroll) {
-        u32x4 v[kUnroll];
+    const int cv = c0 + (c1 - c0) / V * V + tid;  // a value past the last whole vector
+    float rest = -__builtin_inff();
+    if (cv < c1)
+      rest = BF16 ? as_f32((unsigned)reinterpret_cast<const unsigned short*>(rowp)[cv] << 16)
+                  : reinterpret_cast<const float*>(rowp)[cv];
+    auto each = [&](auto f) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const int e = e0 + u * 4 * 256;
-          v[u] = e < c1 ? *reinterpret_cast<const u32x4*>(x + e) : u32x4{0u, 0u, 0u, 0u};
-        }
+      for (int l = 0; l < LOADS; ++l)
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const int e = e0 + u * 4 * 256;
-          if (e >= c1) break;
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            const int k = order_key(v[u][w]);
-            if (k > best_key) { best_key = k; best_idx = e + w; }
+        for (int i = 0; i < 4; ++i) {
+          if (BF16) {
+            f(as_f32(w[l][i] << 16));
+            f(as_f32(w[l][i] & 0xffff0000u));
+          } else {
+            f(as_f32(w[l][i]));
           }
         }
-      }
-    } else {
-      for (int e = c0 + tid; e < c1; e += 256) {
-        const int k = order_key(x[e]);
-        if (k > best_key) { best_key = k; best_idx = e; }
-      }
-    }
-  }
-  // threads that saw no element keep the smallest possible word
-  unsigned long long w = (best_idx == 0x7fffffff) ? 0ull : pack(best_key, best_idx);
-  w = wave_max64(w);
-  if ((tid & 63) == 0) red[tid >> 6] = w;
-  __syncthreads();
-  __shared__ float ent[2][4];
-  __shared__ float s_m;
-  if (tid == 0) {
-    const unsigned long long r = umax64(umax64(red[0], red[1]), umax64(red[2], red[3]));
-    p.part[row * p.chunks + chunk] = r;
-    s_m = key_to_float((int)((unsigned)(r >> 32) ^ 0x80000000u));
-  }
-  if (p.root_entropy == nullptr || row % p.n_nodes != 0) return;
-  // root row: entropy statistics of the chunk relative to its maximum
-  __syncthreads();
-  const float m = s_m;
-  float S = 0.f, T = 0.f;
-  for (int e = c0 + tid; e < c1; e += 256) {
-    const float z = BF16 ? __builtin_bit_cast(float, (unsigned)static_cast<const unsigned short*>(p.logits)[row * (long)p.vocab + e] << 16)
-                         : static_cast<const float*>(p.logits)[row * (long)p.vocab + e];
-    if (z != -__builtin_inff()) {
+      f(rest);
+    };
+    float mc = m;
+    each([&](float z) __attribute__((always_inline)) { mc = fmaxf(mc, z); });
+    entropy_rebase(m, mc, S, T);
+    m = mc;
+    each([&](float z) __attribute__((always_inline)) {
       const float d = z - m;
       const float x = __builtin_amdgcn_exp2f(d * 1.4426950408889634f);
-      S += x;
-      T += x * d;
-    }
+      const bool mass = z != -__builtin_inff();  // -inf carries no probability
+      S += mass ? x : 0.f;
+      T += mass ? x * d : 0.f;
+    });
   }
+  float M = m;
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+  if ((tid & 63) == 0) red_m[tid >> 6] = M;
+  __syncthreads();
+  M = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));
+  entropy_rebase(m, M, S, T);
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     S += __shfl_xor(S, off);
     T += __shfl_xor(T, off);
   }
   if ((tid & 63) == 0) {
-    ent[0][tid >> 6] = S;
-    ent[1][tid >> 6] = T;
+    red_s[tid >> 6] = S;
+    red_t[tid >> 6] = T;
   }
   __syncthreads();
-  if (tid == 0) {
-    const float s_all = (ent[0][0] + ent[0][1]) + (ent[0][2] + ent[0][3]);
-    const float t_all = (ent[1][0] + ent[1][1]) + (ent[1][2] + ent[1][3]);
-    p.ent_part[(row / p.n_nodes) * p.chunks + chunk] = make_float4(m, s_all, t_all, 0.f);
+  if (tid == 0)
+    p.ent_part[(size_t)b * p.ent_chunks + chunk] =
+        make_float4(M, (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]), (red_t[0] + red_t[1]) + (red_t[2] + red_t[3]), 0.f);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
+  __shared__ unsigned long long red[4];
+  // the entropy's workgroups come first, so that they end with the others
+  const int ent_blocks = p.root_entropy ? p.batch * p.ent_chunks : 0;
+  if ((int)blockIdx.x < ent_blocks) {
+    entropy_chunk<BF16>(p, blockIdx.x / p.ent_chunks, blockIdx.x % p.ent_chunks);
+    return;
   }
+  const int block = blockIdx.x - ent_blocks;
+  const int chunk = block % p.chunks;
+  const long row = block / p.chunks;
+  const int c0 = chunk * p.chunk_len;
+  const int c1 = min(p.vocab, c0 + p.chunk_len);
+  constexpr int V = BF16 ? 8 : 4;          // values per 16-byte load
+  const int cv = c0 + (c1 - c0) / V * V;   // end of the whole vectors
+  const int tid = threadIdx.x;
+  int best_key = (int)0x80000000;
+  int best_idx = 0x7fffffff;
+  unsigned long long rest = 0ull;  // the values past them, one a thread
+  if (BF16) {
+    const unsigned short* x = static_cast<const unsigned short*>(p.logits) + row * (long)p.vocab;
+    if (cv + tid < c1) rest = pack(order_key((unsigned int)x[cv + tid] << 16), cv + tid);
+    argmax_bf16_fast(x, c0, cv, tid, best_key, best_idx);
+  } else {
+    const unsigned int* x = static_cast<const unsigned int*>(p.logits) + row * (long)p.vocab;
+    if (cv + tid < c1) rest = pack(order_key(x[cv + tid]), cv + tid);
+    constexpr int kUnroll = 4;
+    for (int e0 = c0 + 4 * tid; e0 < cv; e0 += 4 * 256 * kUnroll) {
+      u32x4 v[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int e = e0 + u * 4 * 256;
+        v[u] = e < cv ? (u32x4)*reinterpret_cast<const u32x4_any*>(x + e) : u32x4{0u, 0u, 0u, 0u};
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int e = e0 + u * 4 * 256;
+        if (e >= cv) break;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int k = order_key(v[u][w]);
+          if (k > best_key) { best_key = k; best_idx = e + w; }
+        }
+      }
+    }
+  }
+  // threads that saw no element keep the smallest possible word
+  unsigned long long w = (best_idx == 0x7fffffff) ? 0ull : pack(best_key, best_idx);
+  w = wave_max64(umax64(w, rest));
+  if ((tid & 63) == 0) red[tid >> 6] = w;
+  __syncthreads();
+  if (tid == 0) p.part[row * p.chunks + chunk] = umax64(umax64(red[0], red[1]), umax64(red[2], red[3]));
 }
 
 // Philox4x32-10: ten rounds of two 32x32 -> 64-bit multiplies and a
@@ -301,44 +360,32 @@ __device__ __forceinline__ int wave_max_key(int v) {
 }
 
 // One group of four tokens as raw words (bf16 pairs, or fp32 bits), loaded a
-// loop iteration ahead and unpacked when used.
-template <bool BF16, bool VEC>
+// loop iteration ahead and unpacked when used; any element alignment.
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+template <bool BF16>
 __device__ __forceinline__ void load_group(const void* rowp, int e4, unsigned (&w)[4]) {
   if (BF16) {
-    const unsigned short* x = static_cast<const unsigned short*>(rowp);
-    if (VEC) {
-      const uint2 v = *reinterpret_cast<const uint2*>(x + e4);
-      w[0] = v.x;
-      w[1] = v.y;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = x[e4 + j];
-    }
+    const u32x2 v = *reinterpret_cast<const u32x2_any*>(static_cast<const unsigned short*>(rowp) + e4);
+    w[0] = v[0];
+    w[1] = v[1];
   } else {
-    const unsigned* x = static_cast<const unsigned*>(rowp);
-    if (VEC) {
-      const uint4 v = *reinterpret_cast<const uint4*>(x + e4);
-      w[0] = v.x;
-      w[1] = v.y;
-      w[2] = v.z;
-      w[3] = v.w;
-    } else {
+    const u32x4 v = *reinterpret_cast<const u32x4_any*>(static_cast<const unsigned*>(rowp) + e4);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = x[e4 + j];
-    }
+    for (int j = 0; j < 4; ++j) w[j] = v[j];
   }
 }
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 __device__ __forceinline__ void unpack_group(const unsigned (&w)[4], float (&z)[4]) {
-  if (BF16 && VEC) {
+  if (BF16) {
     z[0] = __builtin_bit_cast(float, w[0] << 16);
     z[1] = __builtin_bit_cast(float, w[0] & 0xffff0000u);
     z[2] = __builtin_bit_cast(float, w[1] << 16);
     z[3] = __builtin_bit_cast(float, w[1] & 0xffff0000u);
   } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) z[j] = __builtin_bit_cast(float, BF16 ? w[j] << 16 : w[j]);
+    for (int j = 0; j < 4; ++j) z[j] = __builtin_bit_cast(float, w[j]);
   }
 }
 
@@ -428,7 +475,7 @@ __device__ __forceinline__ void sample_group(const AcceptParams& p, const float 
   }
 }
 
-template <bool BF16, bool VEC>
+template <bool BF16>
 __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
   __shared__ unsigned long long red[4];
   __shared__ __align__(16) float s_best[4];  // each wave's running best, shared without barriers
@@ -467,10 +514,10 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
   };
   unsigned wn[4] = {0u, 0u, 0u, 0u};
   if (c0 < full_end) {
-    load_group<BF16, VEC>(rowp, c0 + 4 * tid, wn);
+    load_group<BF16>(rowp, c0 + 4 * tid, wn);
     float z[4];
-    unpack_group<BF16, VEC>(wn, z);
-    if (c0 + 1024 < full_end) load_group<BF16, VEC>(rowp, c0 + 1024 + 4 * tid, wn);
+    unpack_group<BF16>(wn, z);
+    if (c0 + 1024 < full_end) load_group<BF16>(rowp, c0 + 1024 + 4 * tid, wn);
     sample_group<false, true>(p, z, c0 + 4 * tid, c1, node, seq, rnd, wbest, st);
     share();
   }
@@ -479,8 +526,8 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
   int it = 0;
   for (int base = c0 + 1024; base < full_end; base += 1024) {  // the same trip count for every lane
     float z[4];
-    unpack_group<BF16, VEC>(wn, z);
-    if (base + 1024 < full_end) load_group<BF16, VEC>(rowp, base + 1024 + 4 * tid, wn);
+    unpack_group<BF16>(wn, z);
+    if (base + 1024 < full_end) load_group<BF16>(rowp, base + 1024 + 4 * tid, wn);
     sample_group<false, false>(p, z, base + 4 * tid, c1, node, seq, rnd, wbest, st);
     ++it;
     if (it <= 4 || (it & 3) == 0) share();
@@ -502,8 +549,10 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
   if (tid == 0) p.part[row * p.chunks + chunk] = umax64(umax64(red[0], red[1]), umax64(red[2], red[3]));
 }
 
+// Lane v holds row v's token, its node's parent and the edge token, so a step
+// of the walk is a readlane and a ballot, with no memory access; lane k keeps
+// path entry k.
 __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
-  __shared__ int sAm[64];
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
   const int n = p.n_nodes;
@@ -512,6 +561,10 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
   int am = 0;
   int par = -1;
   int tok = 0;
+  // the entropy's chunk statistics go out with the other loads (a lane's first)
+  const float4* ep = p.root_entropy ? p.ent_part + (long)b * p.ent_chunks : nullptr;
+  float4 e0 = {-__builtin_inff(), 0.f, 0.f, 0.f};
+  if (ep && lane < p.ent_chunks) e0 = ep[lane];
   if (lane < n) {
     // the tree and the chunk words are all loaded before any is used (one
     // memory round trip; the argmax store below could alias the tree inputs,
@@ -529,29 +582,26 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
     }
     am = (int)(0xffffffffu - (unsigned int)(w & 0xffffffffull));
     p.argmax_out[rb + lane] = am;
-    sAm[lane] = am;
   }
-  __syncthreads();
 
   // Walk: from node v, descend to the lowest-index child c > v of v whose token
   // is argmax(row v).  Node indices strictly increase, so at most n - 1 steps.
   int v = 0;
   int len = 0;
-  int32_t* path = p.accept_path + (long)b * p.path_stride;
-  if (lane == 0) path[0] = 0;
+  int entry = lane == 0 ? 0 : -1;  // path entry of this lane
   for (int step = 0; step < n; ++step) {
-    const int t = sAm[v];
-    const bool hit = (lane < n) && (lane > v) && (par == v) && (tok == t);
-    const unsigned long long m = __ballot(hit);
+    const int t = __builtin_amdgcn_readlane(am, v);
+    const unsigned long long m = __ballot(lane < n && lane > v && par == v && tok == t);
     if (m == 0ull) break;
-    v = __ffsll((long long)m) - 1;
+    v = (int)__builtin_ctzll(m);
     ++len;
-    if (lane == 0 && len < p.path_stride) path[len] = v;
+    entry = lane == len ? v : entry;
   }
-  for (int k = len + 1 + lane; k < p.path_stride; k += 64) path[k] = -1;
+  int32_t* path = p.accept_path + (long)b * p.path_stride;
+  for (int k = lane; k < p.path_stride; k += 64) path[k] = k < 64 ? entry : -1;
   if (lane == 0) {
     p.accept_len[b] = len;
-    p.next_root[b] = sAm[v];
+    p.next_root[b] = __builtin_amdgcn_readlane(am, v);
   }
   // sampling with a device round counter: every row draw of this call has
   // read it (the draws kernel ran earlier on the stream), so advance it once
@@ -559,21 +609,26 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
     const unsigned r = __hip_atomic_load(p.round_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(p.round_counter, r + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (p.root_entropy && lane == 0) {
-    // merge the chunks relative to the row maximum M:
-    // e^(z-M) (z-M) = e^(m-M) e^(z-m) ((z-m) + (m-M))
-    const float4* ep = p.ent_part + (long)b * p.chunks;
-    float M = -__builtin_inff();
-    for (int c = 0; c < p.chunks; ++c) M = fmaxf(M, ep[c].x);
-    float S = 0.f, T = 0.f;
-    for (int c = 0; c < p.chunks; ++c) {
-      const float4 q = ep[c];
-      if (q.y == 0.f) continue;  // a chunk of -inf logits holds no mass
-      const float f = __builtin_amdgcn_exp2f((q.x - M) * 1.4426950408889634f);
-      S += q.y * f;
-      T += (q.z + (q.x - M) * q.y) * f;
+  if (ep) {
+    // merge the chunks relative to the row maximum M
+    float M = e0.x;
+    for (int c = lane + 64; c < p.ent_chunks; c += 64) M = fmaxf(M, ep[c].x);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    float S = e0.y, T = e0.z;
+    entropy_rebase(e0.x, M, S, T);
+    for (int c = lane + 64; c < p.ent_chunks; c += 64) {
+      float4 q = ep[c];
+      entropy_rebase(q.x, M, q.y, q.z);
+      S += q.y;
+      T += q.z;
     }
-    p.root_entropy[b] = __builtin_amdgcn_logf(S) * 0.6931471805599453f - T / S;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      S += __shfl_xor(S, off);
+      T += __shfl_xor(T, off);
+    }
+    if (lane == 0) p.root_entropy[b] = __builtin_amdgcn_logf(S) * 0.6931471805599453f - T / S;
   }
 }
 
@@ -582,17 +637,9 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
 hipError_t launch_sample(const AcceptParams& p, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const long rows = (long)p.batch * p.n_nodes;
   const dim3 grid((unsigned)(rows * p.chunks)), block(256);
-  const size_t vbytes = bf16 ? 8 : 16;  // one group of four tokens
-  const bool vec = ((size_t)p.vocab * (bf16 ? 2 : 4)) % vbytes == 0 &&
-                   (reinterpret_cast<uintptr_t>(p.logits) % vbytes) == 0;
   if (ev0) (void)hipEventRecord(ev0, s);
-  if (bf16) {
-    if (vec) hipLaunchKernelGGL((sample_partial<true, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((sample_partial<true, false>), grid, block, 0, s, p);
-  } else {
-    if (vec) hipLaunchKernelGGL((sample_partial<false, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((sample_partial<false, false>), grid, block, 0, s, p);
-  }
+  if (bf16) hipLaunchKernelGGL(sample_partial<true>, grid, block, 0, s, p);
+  else hipLaunchKernelGGL(sample_partial<false>, grid, block, 0, s, p);
   hipError_t e = hipGetLastError();
   if (ev1) (void)hipEventRecord(ev1, s);
   if (e != hipSuccess) return e;
@@ -604,17 +651,20 @@ hipError_t launch_sample(const AcceptParams& p, bool bf16, hipStream_t s, hipEve
 
 hipError_t launch_accept(const AcceptParams& p, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const long rows = (long)p.batch * p.n_nodes;
-  const dim3 grid((unsigned)(rows * p.chunks)), block(256);
-  const size_t esz = bf16 ? 2 : 4;
-  const bool vec = ((size_t)p.vocab * esz) % 16 == 0 &&
-                   (reinterpret_cast<uintptr_t>(p.logits) & 15) == 0;
+  const long ent_blocks = p.root_entropy ? (long)p.batch * p.ent_chunks : 0;
+  auto launch = [&](const AcceptParams& q, long blocks) {
+    const dim3 grid((unsigned)blocks), block(256);
+    if (bf16) hipLaunchKernelGGL(argmax_partial<true>, grid, block, 0, s, q);
+    else hipLaunchKernelGGL(argmax_partial<false>, grid, block, 0, s, q);
+  };
   if (ev0) (void)hipEventRecord(ev0, s);
-  if (bf16) {
-    if (vec) hipLaunchKernelGGL((argmax_partial<true, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((argmax_partial<true, false>), grid, block, 0, s, p);
-  } else {
-    if (vec) hipLaunchKernelGGL((argmax_partial<false, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((argmax_partial<false, false>), grid, block, 0, s, p);
+  if (ent_blocks + rows * p.chunks < (1l << 24)) {
+    launch(p, ent_blocks + rows * p.chunks);
+  } else {  // a launch holds fewer than 2^32 threads: the entropy on its own
+    if (ent_blocks) launch(p, ent_blocks);
+    AcceptParams q = p;
+    q.root_entropy = nullptr;
+    launch(q, rows * p.chunks);
   }
   hipError_t e = hipGetLastError();
   if (ev1) (void)hipEventRecord(ev1, s);

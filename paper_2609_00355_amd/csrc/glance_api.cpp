@@ -215,7 +215,9 @@ glance_status attn_common(bool tree, const glance_attn_shape* s, const void* q, 
 struct AcceptPlan {
   int chunks, chunk_len;                // greedy acceptance (bandwidth-bound)
   int sample_chunks, sample_chunk_len;  // sampling walk (ALU-bound: more workgroups)
-  size_t part_bytes, bytes;  // chunk words, then the root row's entropy chunks
+  int ent_chunks, ent_len;              // root entropy: workgroups per root row, values of each
+  size_t ent_off;                       // the entropy's chunk statistics, after the argmax words
+  size_t bytes;
 };
 
 glance_status accept_plan(int32_t batch, int32_t n_nodes, int32_t vocab, AcceptPlan* out) {
@@ -250,8 +252,18 @@ glance_status accept_plan(int32_t batch, int32_t n_nodes, int32_t vocab, AcceptP
   out->sample_chunks = (int)s_chunks;
   out->sample_chunk_len = (int)s_len;
   const long long max_chunks_any = chunks > s_chunks ? chunks : s_chunks;
-  out->part_bytes = round_up((size_t)rows * max_chunks_any * sizeof(unsigned long long), 256);
-  out->bytes = out->part_bytes + round_up((size_t)batch * chunks * sizeof(float4), 256);
+  out->bytes = round_up((size_t)rows * max_chunks_any * sizeof(unsigned long long), 256) +
+               round_up((size_t)batch * chunks * sizeof(float4), 256);
+  // root entropy: a workgroup per kEntropyStep values of a root row, or
+  // several steps each where the statistics would not fit what the greedy
+  // acceptance's own chunk words leave of the workspace (at least one
+  // workgroup per chunk of the argmax fits)
+  out->ent_off = round_up((size_t)rows * chunks * sizeof(unsigned long long), 256);
+  const long long room = (long long)((out->bytes - out->ent_off) / sizeof(float4)) / batch;
+  const long long steps = ((long long)vocab + glance::kEntropyStep - 1) / glance::kEntropyStep;
+  const long long per_wg = (steps + room - 1) / room;
+  out->ent_len = (int)(per_wg * glance::kEntropyStep);
+  out->ent_chunks = (int)((steps + per_wg - 1) / per_wg);
   return ok();
 }
 
@@ -348,7 +360,7 @@ glance_status glance_tree_verify_attn(const glance_attn_shape* s, const void* q,
 
 void bind_accept_workspace(glance::AcceptParams* p, const AcceptPlan& pl, void* workspace) {
   p->part = static_cast<unsigned long long*>(workspace);
-  p->ent_part = reinterpret_cast<float4*>(static_cast<char*>(workspace) + pl.part_bytes);
+  p->ent_part = reinterpret_cast<float4*>(static_cast<char*>(workspace) + pl.ent_off);
 }
 
 // Host checks and parameters shared by the greedy and the sampling
@@ -393,6 +405,8 @@ glance_status accept_setup(int32_t batch, int32_t n_nodes, int32_t vocab, glance
   p->n_nodes = n_nodes;
   p->vocab = vocab;
   p->path_stride = path_stride;
+  p->ent_chunks = pl->ent_chunks;
+  p->ent_len = pl->ent_len;
   return ok();
 }
 

@@ -52,6 +52,9 @@ struct AttnParams {
   int2* plan;       // [batch] (pieces, first piece slot) of each sequence, for the merge pass
 };
 
+// Values of a root row that a workgroup of the root entropy takes at a time.
+constexpr int kEntropyStep = 8192;
+
 struct AcceptParams {
   const void* logits;
   const int32_t* parents;
@@ -62,9 +65,10 @@ struct AcceptParams {
   int32_t* next_root;
   float* root_entropy;       // [batch] or null: entropy of each sequence's row 0
   unsigned long long* part;  // [batch * n_nodes][chunks] packed (key, ~index)
-  float4* ent_part;          // [batch][chunks] (chunk max m, sum e^(z-m), sum e^(z-m) (z-m), 0)
+  float4* ent_part;          // [batch][ent_chunks] (chunk max m, sum e^(z-m), sum e^(z-m) (z-m), 0)
   int batch, n_nodes, vocab, path_stride;
   int chunks, chunk_len;     // chunk_len is a multiple of 8
+  int ent_chunks, ent_len;   // ent_len is a multiple of kEntropyStep
   // sampling walk only: the row draws are argmax(z / temperature + Gumbel)
   float temperature, inv_temperature;
   unsigned seed_lo, seed_hi, round;

@@ -242,3 +242,30 @@ def test_one_workspace_across_calls_and_shapes():
         torch.cuda.synchronize()
         assert int(smp["accept_len"].min()) >= 0
         print(f"[workspace reuse] call {i}: batch {batch} n {n} vocab {vocab} ok", flush=True)
+
+
+# The entropy's workgroups take 8192 values at a time, and rows of any length
+# take unaligned 16-byte loads with up to 7 values left over: the edges of
+# both, more entropy chunks (66) than the walk has lanes, and a batch whose
+# workspace has room for one chunk a sequence (several steps per workgroup).
+@pytest.mark.parametrize("batch,vocab", [(2, 8191), (2, 8192), (2, 8193), (2, 16391), (2, 65 * 8192 + 9), (410, 20483)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_entropy_and_argmax_at_chunk_edges(batch, vocab, dtype):
+    g = torch.Generator().manual_seed(vocab)
+    n = 5
+    logits = torch.randn((batch, n, vocab), generator=g).to(dtype)
+    at = [[0, vocab - 1, vocab - 2, vocab // 8 * 8, vocab // 8 * 8 - 1], [vocab - 1, 8190, 1, vocab - 3, 0]]
+    at = [[min(t, vocab - 1) for t in at[b % 2]] for b in range(batch)]
+    for b in range(batch):
+        for v in range(n):
+            logits[b, v, at[b][v]] = 9.0
+    logits[1, 0, : vocab // 2] = float("-inf")  # whole entropy chunks without mass
+    par = torch.tensor([[-1, 0, 1, 2, 3]] * batch, dtype=torch.int32)
+    tok = torch.tensor([[7] + row[:-1] for row in at], dtype=torch.int32)
+    res = G.glance_greedy_accept(logits.cuda(), par.cuda(), tok.cuda(), want_entropy=True)
+    got = {k: res[k].cpu().numpy() for k in ("argmax", "accept_len", "accept_path", "next_root")}
+    assert got["argmax"].tolist() == at
+    assert_accept_equal(got, logits, par, tok)
+    for b in range(batch):
+        ref = OA.row_entropy(logits[b, 0])
+        assert abs(float(res["root_entropy"][b]) - ref) <= 2e-4 + 2e-5 * abs(ref)
