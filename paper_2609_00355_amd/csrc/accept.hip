@@ -290,15 +290,18 @@ __global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
 
 // Philox4x32-10: ten rounds of two 32x32 -> 64-bit multiplies and a
 // counter shuffle, the key advanced by the Weyl constants between rounds.
-__device__ __forceinline__ void philox4x32_10(unsigned (&c)[4], unsigned k0, unsigned k1) {
+// c[0]'s product of the first round comes in as p0: the caller's counters are
+// an arithmetic sequence, so that it is an addition there.
+constexpr unsigned kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
+__device__ __forceinline__ void philox4x32_10(unsigned long long p0, unsigned (&c)[4], unsigned k0, unsigned k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r > 0) {
       k0 += 0x9E3779B9u;
       k1 += 0xBB67AE85u;
+      p0 = (unsigned long long)kPhiloxM0 * c[0];
     }
-    const unsigned long long p0 = (unsigned long long)0xD2511F53u * c[0];
-    const unsigned long long p1 = (unsigned long long)0xCD9E8D57u * c[2];
+    const unsigned long long p1 = (unsigned long long)kPhiloxM1 * c[2];
     // three-input XOR in one v_bitop3_b32 (truth table 0x96)
     const unsigned n0 = __builtin_amdgcn_bitop3_b32((unsigned)(p1 >> 32), c[1], k0, 0x96);
     const unsigned n2 = __builtin_amdgcn_bitop3_b32((unsigned)(p0 >> 32), c[3], k1, 0x96);
@@ -390,22 +393,28 @@ __device__ __forceinline__ void unpack_group(const unsigned (&w)[4], float (&z)[
 }
 
 // Row draws of the sampling walk.  Evaluating both logarithms for every token
-// would cost about a hundred instructions a token, so each token is first
-// tested against the wave's running best y* (the largest z / T + g found so
-// far by any lane of the wave) with an upper bound on its noise read off the
-// uniform's integer: with u = (k + 0.5) 2^-23, r = 2^23 - 1 - k and x the
-// generator word (k = x >> 9), g <= -ln(1 - u) <= (23 - log2 r) ln 2, and
-// log2 r >= F 2^-23 - 127 with F the fp32 bits of float(r) (its exponent plus
-// mantissa fraction, since log2(1 + f) >= f on [0, 1]); on average the bound
-// sits within 0.46 of the noise, and the fixed recipe stays below it.  A token is skipped only when
-// z / T plus that bound plus a margin for every rounding involved (2^-17
-// relative, 2^-12 absolute) is still below y*: then a strictly larger value
-// exists and the token cannot be the draw.  Before the generator runs, the
-// largest bound, 24 ln 2, tests the group's largest logit (NaN-propagating)
-// to skip whole groups of four.  -inf logits are clamped to -FLT_MAX for the
-// group test, so fully masked groups are skipped once y* is finite.  Survivors take the
-// exact definition.  (A -inf logit inside a group with finite ones gives a NaN
-// bound and takes the exact path: slower, never wrong.)
+// would cost about a hundred instructions a token, so each group of four is
+// first tested against the wave's running best y* (the largest z / T + g found
+// so far by any lane of the wave).  Let m be the group's largest z / T and x
+// = m - y* plus an allowance for every rounding involved (2^-17 relative,
+// 2^-12 absolute).  A token can only win if its noise g >= -x; with
+// u = (k + 0.5) 2^-23, r = 2^23 - 1 - k and c the generator word (k = c >> 9),
+// g <= -ln(1 - u) and 1 - u > r 2^-23, so it takes r <= R = 2^23 e^x, that is
+// ~c <= 512 R + 511.  So one exponential per group gives a threshold T (a
+// thousandth and 512 larger, for the roundings), and the group is skipped if
+// the largest of its four words is below ~T: then a strictly larger value
+// exists and none of its tokens is the draw.  With x < -24 ln 2 no word can
+// pass, and the group skips the generator too.  In a group that passes, each
+// token is tested with its own z / T and the bound log2 r >= F 2^-23 - 127, F
+// the fp32 bits of float(r) (exponent plus mantissa fraction, since
+// log2(1 + f) >= f on [0, 1]); survivors take the exact definition.  NaN or
+// infinite operands give a T that every word passes, and a NaN bound takes the
+// exact path: slower, never wrong.  -inf logits are clamped to -FLT_MAX for
+// the group test, so fully masked groups are skipped once y* is finite.
+//
+// Bound by instruction issue, most of it the generator's 17 quarter-rate
+// 64-bit multiplies a group.  4 x 64 x 152064 bf16, T = 1: 33.7 us with a
+// bound per token (11 instructions each), SAMPLE_AFTER us with one per group.
 struct SampleState {
   int best_key, best_idx;
   float lane_best;  // y of the lane's best token
@@ -421,23 +430,21 @@ struct SampleState {
 // token reaching it is never skipped, so the exact draw is kept.
 template <bool TAIL, bool FIRST>
 __device__ __forceinline__ void sample_group(const AcceptParams& p, const float (&z)[4], int e4, int c1,
-                                             unsigned node, unsigned seq, unsigned rnd, float& wbest,
-                                             SampleState& st) {
+                                             unsigned long long m0c, unsigned node, unsigned seq, unsigned rnd,
+                                             float& wbest, SampleState& st) {
   constexpr float kLn2 = 0.6931472f;
+  constexpr float kLog2e = 1.442695041f;
   const float inv_t = p.inv_temperature;
+  const float m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(z[0], z[1]),
+                                                __builtin_elementwise_maximum(z[2], z[3]));
+  const float mt = __builtin_elementwise_maximum(m * inv_t, -3.4028234663852886e38f);
+  const float mt_hi = fmaf(fabsf(mt), 0x1p-17f, mt);
   if (!FIRST) {
-    // group test with the largest bound
-    const float slack = fmaf(fabsf(wbest), 0x1p-17f, 0x1p-12f);
-    float m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(z[0], z[1]),
-                                            __builtin_elementwise_maximum(z[2], z[3]));
-    float mt = m * inv_t;
-    mt = mt == -__builtin_inff() ? -3.4028234663852886e38f : mt;
-    const bool group_beaten = fmaf(fabsf(mt), 0x1p-17f, mt) + (slack + 24.f * kLn2) < wbest;
-    if (group_beaten && !TAIL) return;
-    if (TAIL && (group_beaten || e4 >= c1)) return;
+    const bool beaten = mt_hi + (fmaf(fabsf(wbest), 0x1p-17f, 0x1p-12f) - wbest) < -24.f * kLn2;
+    if (beaten || (TAIL && e4 >= c1)) return;
   }
   unsigned c[4] = {(unsigned)e4 >> 2, node, seq, rnd};
-  philox4x32_10(c, p.seed_lo, p.seed_hi);
+  philox4x32_10(m0c, c, p.seed_lo, p.seed_hi);
   if (FIRST) {
     int lo_key = (int)0x80000000;
 #pragma unroll
@@ -453,13 +460,18 @@ __device__ __forceinline__ void sample_group(const AcceptParams& p, const float 
     wbest = __builtin_bit_cast(float, float_order(wave_max_key(lo_key)));
   }
   const float slack = fmaf(fabsf(wbest), 0x1p-17f, 0x1p-12f);
+  // T = 512 R (1 + 2^-10) + 1024, saturating; a NaN x passes everything (the
+  // minimum takes the other operand)
+  const float x = mt_hi + (slack - wbest);
+  const float t = __builtin_amdgcn_exp2f(fmaf(fminf(x, 0.f), kLog2e, 32.00141f)) + 1024.f;
+  unsigned T;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(T) : "v"(t));  // saturates, unlike a cast
+  if (max(max(c[0], c[1]), max(c[2], c[3])) < ~T) return;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     if (TAIL && e4 + j >= c1) break;
     const float zt = z[j] * inv_t;
-    // upper bound on the noise: g <= -ln(1 - u) <= (23 - log2 r) ln 2 with
-    // r = 2^23 - 1 - k, log2 r bounded below by the fp32 bits of float(r)
-    // read as exponent plus mantissa fraction (r = 0: 150 ln 2)
+    // the noise's upper bound from its own word (r = 0: 150 ln 2)
     const unsigned r = 0x7FFFFFu - (c[j] >> 9);
     const float lg2r = (float)__builtin_bit_cast(unsigned, (float)r) * 0x1p-23f - 127.f;
     const float bound = fmaf(23.f - lg2r, kLn2, fmaf(fabsf(zt), 0x1p-17f, zt) + slack);
@@ -513,12 +525,14 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
     wbest = o > wbest ? o : wbest;
   };
   unsigned wn[4] = {0u, 0u, 0u, 0u};
+  // the generator's first product, M0 times the counter, of the lane's group
+  unsigned long long m0c = (unsigned long long)kPhiloxM0 * (unsigned)((c0 >> 2) + tid);
   if (c0 < full_end) {
     load_group<BF16>(rowp, c0 + 4 * tid, wn);
     float z[4];
     unpack_group<BF16>(wn, z);
     if (c0 + 1024 < full_end) load_group<BF16>(rowp, c0 + 1024 + 4 * tid, wn);
-    sample_group<false, true>(p, z, c0 + 4 * tid, c1, node, seq, rnd, wbest, st);
+    sample_group<false, true>(p, z, c0 + 4 * tid, c1, m0c, node, seq, rnd, wbest, st);
     share();
   }
   // the running best is exchanged every iteration while it still climbs fast,
@@ -528,7 +542,8 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
     float z[4];
     unpack_group<BF16>(wn, z);
     if (base + 1024 < full_end) load_group<BF16>(rowp, base + 1024 + 4 * tid, wn);
-    sample_group<false, false>(p, z, base + 4 * tid, c1, node, seq, rnd, wbest, st);
+    m0c += (unsigned long long)kPhiloxM0 * 256u;  // 1024 tokens on
+    sample_group<false, false>(p, z, base + 4 * tid, c1, m0c, node, seq, rnd, wbest, st);
     ++it;
     if (it <= 4 || (it & 3) == 0) share();
   }
@@ -540,7 +555,7 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
       z[j] = e4 + j < c1 ? (BF16 ? __builtin_bit_cast(float, (unsigned)reinterpret_cast<const unsigned short*>(rowp)[e4 + j] << 16)
                                  : reinterpret_cast<const float*>(rowp)[e4 + j])
                          : -__builtin_inff();
-    sample_group<true, false>(p, z, e4, c1, node, seq, rnd, wbest, st);
+    sample_group<true, false>(p, z, e4, c1, (unsigned long long)kPhiloxM0 * ((unsigned)e4 >> 2), node, seq, rnd, wbest, st);
   }
   unsigned long long w = (st.best_idx == 0x7fffffff) ? 0ull : pack(st.best_key, st.best_idx);
   w = wave_max64(w);

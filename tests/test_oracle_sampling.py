@@ -152,6 +152,30 @@ def test_sampling_walk_preserves_the_target_distribution():
     assert stats.chisquare(obs, np.array(exp) * sum(obs) / sum(exp)).pvalue > 1e-3
 
 
+def test_group_threshold_on_the_generator_word():
+    """A token can only reach the running best if its noise g is at least -x,
+    x the group's distance to it.  With T = 512 2^23 e^x (1 + 2^-10) + 1024 as
+    the sampler computes it (fp32, saturating to 32 bits), every word c with
+    that noise has ~c <= T, so a group whose words all have ~c > T holds no
+    draw.  Checked for every k = c >> 9 at the smallest x for which it can win
+    (x = -g, less half the sampler's absolute allowance of 2^-12), for the
+    word with the largest ~c.  One exponential ulp is 2^-13 of the 2^-10 kept."""
+    k = np.arange(2 ** 23, dtype=np.uint32)
+    u = (k.astype(np.float32) + np.float32(0.5)) * np.float32(2.0 ** -23)
+    g = S.gumbel(u)
+    x = np.minimum(-g + np.float32(2.0 ** -13), np.float32(0.0))
+    t = np.exp2(x * np.float32(1.442695041) + np.float32(32.00141)).astype(np.float32) * np.float32(1 - 2.0 ** -13)
+    T = np.minimum(np.floor(t.astype(np.float64) + 1024.0), 2.0 ** 32 - 1).astype(np.uint64)
+    not_c = (~(k << np.uint32(9))).astype(np.uint64)
+    assert np.all(not_c <= T)
+    # and it is a threshold: with x three below, at most a tenth of the words
+    # that cannot win pass
+    x3 = np.minimum(-g - np.float32(3.0), np.float32(0.0))
+    t3 = np.exp2(x3 * np.float32(1.442695041) + np.float32(32.00141))
+    up = g > 0.0
+    assert np.mean(not_c[up] <= t3[up].astype(np.float64) + 1024.0) < 0.1
+
+
 def test_gumbel_bound_by_leading_zeros():
     """g(u) <= -ln(1 - u) <= (clz(r) - 8) ln 2 with r = 2^23 - 1 - k for the
     uniform u = (k + 0.5) 2^-23 (since -ln u >= 1 - u and 1 - u >= r 2^-23).
