@@ -414,7 +414,7 @@ __device__ __forceinline__ void unpack_group(const unsigned (&w)[4], float (&z)[
 //
 // Bound by instruction issue, most of it the generator's 17 quarter-rate
 // 64-bit multiplies a group.  4 x 64 x 152064 bf16, T = 1: 33.7 us with a
-// bound per token (11 instructions each), SAMPLE_AFTER us with one per group.
+// bound per token (11 instructions each), 30.3 us with one per group.
 struct SampleState {
   int best_key, best_idx;
   float lane_best;  // y of the lane's best token

@@ -38,7 +38,7 @@
 // workspace, and attn_merge.hip combines the pieces in a second, fully
 // parallel pass; the first piece of each sequence records the sequence's
 // piece count and first slot for it.
-#include "glance_internal.h"
+#include "attn_plan.h"
 
 namespace glance {
 namespace {
@@ -121,112 +121,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 // s_barrier.  (__syncthreads() also waits for every outstanding global load,
 // which would drain the ring.)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
-  return v;
-}
-
-__device__ __forceinline__ int clamp_ctx(int ctx, int cap) { return ctx < 0 ? 0 : (ctx > cap ? cap : ctx); }
-// tiles of a sequence: its context tiles, then the tile of new keys
-__device__ __forceinline__ int seq_tiles(int ctx) { return (ctx + 63) / 64 + 1; }
-
-struct Piece {
-  int b;        // sequence
-  int first;    // piece slot of the sequence's first piece (within the KV head)
-  int count;    // pieces of the sequence
-  int index;    // this piece's index among them
-  int t_begin;  // first tile (of the sequence's tile list)
-  int n_tiles;  // tiles of the piece, >= 1
-  int ctx;      // context keys of the sequence
-};
-
-// The piece plan (identical in every wave of every workgroup): T is the
-// smallest piece size, at least min_tiles, with sum_b ceil(len_b / T) <=
-// slots; piece slot ps then names piece ps - first_b of the sequence b with
-// first_b <= ps < first_b + n_b.  Returns false if the slot is unused.  The
-// lengths are read once (sequences lane + 64 k, k < kPlanCache, held in
-// registers; larger batches re-read the rest), since every memory round trip
-// here delays the first tile load.
-constexpr int kPlanCache = 4;
-__device__ bool find_piece(const AttnParams& p, int ps, int lane, Piece& out) {
-  int len_c[kPlanCache], ctx_c[kPlanCache];
-#pragma unroll
-  for (int k = 0; k < kPlanCache; ++k) {
-    const int b = lane + 64 * k;
-    ctx_c[k] = b < p.batch ? clamp_ctx(p.ctx_lens[b], p.cap) : 0;
-    len_c[k] = b < p.batch ? seq_tiles(ctx_c[k]) : 0;
-  }
-  auto len_of = [&](int k, int b) __attribute__((always_inline)) {
-    return k < kPlanCache ? len_c[k] : (b < p.batch ? seq_tiles(clamp_ctx(p.ctx_lens[b], p.cap)) : 0);
-  };
-  int total = 0, longest = 0;
-  for (int b0 = 0, k = 0; b0 < p.batch; b0 += 64, ++k) {
-    const int len = len_of(k, b0 + lane);
-    total += len;
-    longest = max(longest, len);
-  }
-  total = wave_sum(total);
-  longest = wave_max(longest);
-  const int slots = p.slots_per_g;
-  auto count = [&](int T) __attribute__((always_inline)) {
-    int cnt = 0;
-    for (int b0 = 0, k = 0; b0 < p.batch; b0 += 64, ++k) cnt += (len_of(k, b0 + lane) + T - 1) / T;
-    return wave_sum(cnt);
-  };
-  int lo = max(p.min_tiles, (total + slots - 1) / slots);
-  int hi = max(lo, longest);  // with T = longest every sequence is one piece; slots >= batch
-  if (count(lo) <= slots) hi = lo;  // exact for equal lengths
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (count(mid) <= slots) hi = mid;
-    else lo = mid + 1;
-  }
-  const int T = __builtin_amdgcn_readfirstlane(lo);
-  int base = 0;
-  for (int b0 = 0, k = 0; b0 < p.batch; b0 += 64, ++k) {
-    const int b = b0 + lane;
-    const int ctx = k < kPlanCache ? ctx_c[k] : (b < p.batch ? clamp_ctx(p.ctx_lens[b], p.cap) : 0);
-    const int len = b < p.batch ? seq_tiles(ctx) : 0;
-    const int nb = (len + T - 1) / T;
-    int incl = nb;  // inclusive prefix sum over the lanes
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off);
-      if (lane >= off) incl += v;
-    }
-    incl += base;
-    const int excl = incl - nb;
-    const unsigned long long hit = __ballot(b < p.batch && excl <= ps && ps < incl);
-    if (hit) {
-      const int src = __ffsll((long long)hit) - 1;
-      out.b = b0 + src;
-      out.first = __shfl(excl, src);
-      out.count = __shfl(nb, src);
-      out.ctx = __shfl(ctx, src);
-      const int slen = __shfl(len, src);
-      out.index = ps - out.first;
-      out.t_begin = out.index * slen / out.count;
-      out.n_tiles = (out.index + 1) * slen / out.count - out.t_begin;
-      out.b = __builtin_amdgcn_readfirstlane(out.b);
-      out.first = __builtin_amdgcn_readfirstlane(out.first);
-      out.count = __builtin_amdgcn_readfirstlane(out.count);
-      out.ctx = __builtin_amdgcn_readfirstlane(out.ctx);
-      out.index = __builtin_amdgcn_readfirstlane(out.index);
-      out.t_begin = __builtin_amdgcn_readfirstlane(out.t_begin);
-      out.n_tiles = __builtin_amdgcn_readfirstlane(out.n_tiles);
-      return true;
-    }
-    base = __shfl(incl, 63);
-  }
-  return false;
-}
 
 template <int D, bool TREE>
 __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
@@ -398,23 +292,8 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   int par = -1;
   if (tree_words && lane < p.n) par = p.parents[(size_t)b * p.n + lane];
   ring_wait(0);
-  // ancestor words of the packed tree, anc[i] = {i} u anc[parent(i)], by
-  // pointer doubling in wave 0: after r rounds lane i holds its root path
-  // from i up to (excluding) its 2^r-th ancestor up[i]
   if (tree_words) {
-    int up = (par >= 0 && par < lane) ? par : -1;
-    unsigned long long anc = 1ull << lane;
-#pragma unroll
-    for (int r = 0; r < 6; ++r) {
-      const int src = up < 0 ? lane : up;
-      const unsigned lo = __shfl((unsigned)anc, src);
-      const unsigned hi = __shfl((unsigned)(anc >> 32), src);
-      const int up2 = __shfl(up, src);
-      if (up >= 0) {
-        anc |= ((unsigned long long)hi << 32) | lo;
-        up = up2;
-      }
-    }
+    const unsigned long long anc = ancestor_word(par, lane);
     if (lane < p.n) sAnc[lane] = anc;  // read after the tile barriers
   }
 
