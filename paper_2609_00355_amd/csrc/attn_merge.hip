@@ -22,7 +22,7 @@
 // consecutive threads read consecutive lanes, 512 bytes per wave-wide load.
 // Sequences with one piece were written by the attention kernel and are
 // skipped.
-#include "glance_internal.h"
+#include "attn_plan.h"
 
 namespace glance {
 namespace {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_merge_kernel(AttnParams
   }
 #pragma unroll
   for (int off = LPR / 2; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
-  if (!live) return;
+  if (!live || nsb == 1) return;  // one split: written by the attention kernel
   const float inv = 1.f / lsum;
   if (BF16) {
     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_merge_kernel(AttnParams
     *reinterpret_cast<float4*>(static_cast<float*>(p.out) + (size_t)row * D + 4 * q) =
         float4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
   }
-  if (p.lse && q == 0) p.lse[row] = (M + log2f(lsum)) * kLn2;
+  if (p.lse && q == 0) p.lse[row] = log_sum(M, lsum);
 }
 
 

@@ -1,5 +1,6 @@
 // What the attention kernels share: the piece plan of a call's keys, derived
-// on the device from ctx_lens, and the ancestor words of a packed tree.
+// on the device from ctx_lens, the ancestor words of a packed tree, and the
+// fp32 path's log-sum-exp.
 #pragma once
 
 #include "glance_internal.h"
@@ -59,6 +60,16 @@ struct Piece {
   int n_tiles;  // tiles of the piece, >= 1
   int ctx;      // context keys of the sequence
 };
+
+// ln(2^M sum) of the fp32 path.  The reference M need not be the row maximum,
+// so log2(sum) may be as large as the result and its rounding as coarse: the
+// logarithm is taken of the sum's fraction and every larger term enters by a
+// fused multiply-add, which leaves little more than the result's own rounding.
+__device__ __forceinline__ float log_sum(float M, float sum) {
+  constexpr float ln2 = 0.6931471805599453f;
+  const float frac = log2f(__builtin_amdgcn_frexp_mantf(sum)) * ln2;
+  return fmaf((float)__builtin_amdgcn_frexp_expf(sum), ln2, fmaf(M, ln2, frac));
+}
 
 // The piece plan (identical in every wave of every workgroup): T is the
 // smallest piece size, at least min_tiles, with sum_b ceil(len_b / T) <=

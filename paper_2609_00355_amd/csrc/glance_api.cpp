@@ -37,18 +37,34 @@ bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u
 
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// fp32 kernel: context keys per split, about one workgroup per compute unit
-// over the whole grid, at least 256 and at most 8192 keys per split.
-// Context keys per split of the fp32 kernel: about 256 workgroups over the
-// capacity, at least one key tile (a workgroup walks its tiles one after
-// another, so small shapes finish sooner in more, shorter splits).
-int f32_split_keys(const glance_attn_shape& s, int row_groups) {
-  const long long cap = s.ctx_capacity > 0 ? s.ctx_capacity : 1;
-  long long per = cap * s.batch * s.n_kv_heads * row_groups / 256;
-  per = (per + glance::kKeyTile - 1) / glance::kKeyTile * glance::kKeyTile;
-  if (per < glance::kKeyTile) per = glance::kKeyTile;
-  if (per > 8192) per = 8192;
-  return (int)per;
+// fp32 kernel: rows per row tile and context keys per split.  A workgroup's
+// time is its keys over its waves; a second split costs the merge launch
+// (about 5 us).
+//  - Work that fits one workgroup of eight waves per compute unit at 128 keys
+//    each takes 16-row tiles: the finest cut, since it is latency that counts.
+//    Up to 256 keys of 128 dims (512 of 64) a single split ends sooner than
+//    several and a merge (16 rows, 8/1 heads of 128: 11.5 us at 256 keys; at
+//    456 keys 17.7 us with one split, 12.4 with four); longer contexts take
+//    splits of 128 keys (256 of 64 dims), one round of the waves' blocks.
+//  - More work takes 32-row tiles, half the K/V reads per row, in workgroups
+//    of four waves: as many equal splits (the new keys counted in) as fill
+//    one workgroup per compute unit (measured: two take 55 us instead of 48 at
+//    64 rows, 28/4 heads of 128, 4096 keys).  At most 4096 keys each, so that
+//    a ragged batch ends evenly.
+void plan_f32(const glance_attn_shape& s, int rows, int* rows_rg, int* split_keys) {
+  const long long keys = (long long)s.ctx_capacity + s.n_new;
+  const long long problems = (long long)s.batch * s.n_kv_heads;
+  long long per;
+  if (problems * ((rows + 15) / 16) * ((keys + 127) / 128) <= 256) {
+    *rows_rg = 16;
+    per = keys <= 32768 / s.head_dim ? keys : 16384 / s.head_dim;
+  } else {
+    *rows_rg = 32;
+    const long long splits = 256 / (problems * ((rows + 31) / 32));
+    per = splits > 1 ? (keys + splits - 1) / splits : keys;
+    per = per < 64 ? 64 : per > 4096 ? 4096 : per;
+  }
+  *split_keys = (int)((per + 15) / 16 * 16);
 }
 
 // Attention workspace: [piece table][(max, sum) partials][O partials].
@@ -130,9 +146,9 @@ glance_status make_plan(const glance_attn_shape* s, Plan* out) {
     pl.part_ml_bytes = round_up(wslots * p.rows_rg * sizeof(float2), 256);
     pl.part_o_bytes = round_up(wslots * p.rows_rg * p.d * sizeof(uint16_t), 256);  // fp16
   } else {
-    p.row_groups = (p.rows + glance::kF32RowBlock - 1) / glance::kF32RowBlock;
-    p.rows_pad = p.row_groups * glance::kF32RowBlock;
-    p.split_keys = f32_split_keys(*s, p.row_groups);
+    plan_f32(*s, p.rows, &p.rows_rg, &p.split_keys);
+    p.row_groups = (p.rows + p.rows_rg - 1) / p.rows_rg;
+    p.rows_pad = p.row_groups * p.rows_rg;
     p.nsplit = p.cap > 0 ? (p.cap + p.split_keys - 1) / p.split_keys : 1;
     const size_t slots = (size_t)p.batch * p.hkv * p.nsplit * p.rows_pad;
     pl.counter_bytes = 0;
@@ -207,6 +223,7 @@ glance_status attn_common(bool tree, const glance_attn_shape* s, const void* q, 
   hipError_t e = s->dtype == GLANCE_BF16 ? glance::launch_attn_bf16(p, tree, stream, e0, e1)
                                          : glance::launch_attn_f32(p, tree, stream, e0, e1);
   if ((st = check_hip(e, "attention kernel launch")) != GLANCE_OK) return st;
+  if (s->dtype == GLANCE_F32 && p.nsplit == 1) return ok();  // every workgroup wrote its rows' output
   e = s->dtype == GLANCE_BF16 ? glance::launch_attn_merge_pieces(p, stream)
                               : glance::launch_attn_merge(p, false, stream);
   return check_hip(e, "merge kernel launch");

@@ -7,13 +7,6 @@
 
 namespace glance {
 
-// Keys per LDS tile and waves per workgroup of the attention kernels.
-constexpr int kKeyTile = 64;
-constexpr int kWaves = 4;
-// Rows per workgroup of the fp32 attention kernel (kWaves waves x 8 rows).
-constexpr int kF32RowsPerWave = 8;
-constexpr int kF32RowBlock = kWaves * kF32RowsPerWave;
-
 // Everything a split-KV attention launch needs.  Layouts:
 //   q      [batch][n][hq][d]         k_ctx/v_ctx [batch][hkv][cap][d]
 //   k_new  [batch][n][hkv][d]        parents [batch][n]
@@ -42,13 +35,13 @@ struct AttnParams {
   int rows_pad;   // rows rounded up to the kernel's row block (fp32 kernel)
   int row_groups; // workgroups sharing one run of key tiles
   int nsplit;     // split slots per (sequence, KV head) = ceil(cap / split_keys), >= 1 (fp32 kernel)
-  int split_keys; // context keys per split, multiple of kKeyTile (fp32 kernel)
+  int split_keys; // context keys per split, a multiple of 16 (fp32 kernel)
   float scale_log2;  // sm_scale * log2(e)
   // bf16 kernel: pieces planned on the device from ctx_lens (see attn_bf16.hip)
   int slots_per_g;  // piece slots per KV head (>= batch)
   int min_tiles;    // smallest piece, in 64-key tiles
   int tiles_rg;     // 32-row tiles per row group (= computing waves, 1..7)
-  int rows_rg;      // 32 * tiles_rg
+  int rows_rg;      // 32 * tiles_rg; fp32 kernel: rows of a row tile, 16 or 32
   int2* plan;       // [batch] (pieces, first piece slot) of each sequence, for the merge pass
 };
 

@@ -38,7 +38,7 @@ def _check(kind, w, ctx_lens, n, seed=0, variant=None, poison=False, tree_shape=
     return assert_close(out, lse, ref_out, ref_lse, w.dtype, what)
 
 
-# ------------------------------------------------------------- fp32 (VALU path)
+# ------------------------------------------------------------- fp32 (fp32 matrix path)
 def test_tiny_fp32_draft_and_verify():
     w = C.WORKLOADS["tiny_fp32"]
     ctx = C.context_lengths(w)
@@ -67,6 +67,23 @@ def test_fp32_tree_shapes(shape):
     w = _w("tiny_fp32", n_tree=40, depth_cap=39)
     _check("verify", w, [77, 0], 40, seed=3, variant="tree_dominant", tree_shape=shape,
            what=f"fp32 {shape}")
+
+
+# The fp32 kernel's cuts: blocks of 16 keys dealt to 8 waves (16-row tiles,
+# one split up to 32768 / D keys, then splits of 16384 / D) or to 4 waves
+# (32-row tiles, where 16-row tiles of 128 keys would pass 256 workgroups).
+@pytest.mark.parametrize("d,hq,hkv,n,ctx,cap", [
+    (128, 8, 1, 16, [240], 240),               # 256 keys: one split
+    (128, 8, 1, 16, [241, 17], 241),           # 257: splits of 128, the second sequence in one
+    (64, 4, 1, 33, [479, 512, 1], 512),        # splits of 256 of 64 dims, a full last split
+    (64, 6, 3, 17, [15, 16, 31], 40),          # block edges, fewer blocks than waves
+    (128, 28, 4, 47, [1300, 0, 777], 1500),    # 32-row tiles, padded rows, ragged, a split past a sequence
+    (64, 28, 4, 64, [2049], 3000),             # 32-row tiles of 64 dims
+])
+def test_fp32_splits_and_row_tiles(d, hq, hkv, n, ctx, cap):
+    w = _w("tiny_fp32", d=d, hq=hq, hkv=hkv, batch=len(ctx))
+    for kind in ("draft", "verify"):
+        _check(kind, w, ctx, n, seed=14, variant="sharp1", poison=True, cap=cap, what=f"fp32 cuts d{d} n{n}")
 
 
 # ------------------------------------------------------------- bf16 (MFMA path)
