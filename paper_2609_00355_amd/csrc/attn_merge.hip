@@ -18,10 +18,12 @@
 // (max, sum) pair carries (lane l of a 32-row tile holds row l % 32 and, in
 // quad k, dims 32 (k / 4) + 8 (k % 4) + 4 (l / 32) .. +3).  A thread owns one
 // (row, four dims) and reads that quad of every piece of its sequence, in
-// piece order, all loads of a chunk of 16 pieces issued before any is used;
+// piece order, all loads of a chunk of pieces issued before any is used;
 // consecutive threads read consecutive lanes, 512 bytes per wave-wide load.
 // Sequences with one piece were written by the attention kernel and are
-// skipped.
+// skipped.  Bound by latency (two memory round trips after the launch): the
+// only sequence of a batch of one starts at slot 0, so its first chunk's loads
+// go out beside the plan's, before the piece count is known.
 #include "attn_plan.h"
 
 namespace glance {
@@ -106,11 +108,10 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_merge_kernel(AttnParams
 }
 
 
-template <int D>
+template <int D, int kChunk>
 __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
   constexpr int KQ = D / 8;    // quads of values per lane of a tile (OV / 4)
   constexpr int WG_K = 4;      // quad slots per workgroup (one per wave)
-  constexpr int kChunk = 16;
   const int lane = threadIdx.x & 63;
   const int k = (blockIdx.x % (KQ / WG_K)) * WG_K + (threadIdx.x >> 6);
   int unit = blockIdx.x / (KQ / WG_K);  // ((b * hkv + g) * row_groups + rgi) * tiles_rg + w
@@ -121,48 +122,62 @@ __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
   const int g = unit % p.hkv;
   const int b = unit / p.hkv;
   const int2 pl = p.plan[b];  // (pieces, first slot)
-  if (pl.x <= 1) return;
   const int r32 = lane & 31, h = lane >> 5;
   const int row = 32 * (rgi * p.tiles_rg + w) + r32;
-  if (row >= p.rows) return;
-  const int node = row / p.group;
-  const size_t out_row = ((size_t)b * p.n + node) * p.hq + (size_t)g * p.group + (row - node * p.group);
-  const int d0 = 32 * (k >> 2) + 8 * (k & 3) + 4 * h;
-
-  const size_t ws0 = ((size_t)g * p.slots_per_g + pl.y) * p.row_groups + rgi;  // piece q: ws0 + q * row_groups
-  const size_t o_stride = (size_t)p.row_groups * p.tiles_rg * KQ * 64;          // fp16 quads between pieces
+  const bool live = row < p.rows;
+  const size_t o_stride = (size_t)p.row_groups * p.tiles_rg * KQ * 64;  // fp16 quads between pieces
   const size_t ml_stride = (size_t)p.row_groups * p.rows_rg;
-  const f16x4* po = reinterpret_cast<const f16x4*>(p.part_o) + (ws0 * p.tiles_rg + w) * KQ * 64 + k * 64 + lane;
-  const float2* pm = p.part_ml + ws0 * p.rows_rg + 32 * w + r32;
 
   float M = -__builtin_inff(), lsum = 0.f;
   float4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int q0 = 0; q0 < pl.x; q0 += kChunk) {
-    const int cnt = min(kChunk, pl.x - q0);
-    float2 ml[kChunk];
-    f16x4 v[kChunk];
+  float2 ml[kChunk];
+  f16x4 v[kChunk];
+  // the (max, sum) pairs and output quads of up to `cnt` pieces from slot
+  // `slot` on, all loads issued before any is used
+  auto load = [&](int slot, int cnt) __attribute__((always_inline)) {
+    const size_t ws = ((size_t)g * p.slots_per_g + slot) * p.row_groups + rgi;  // piece u: ws + u * row_groups
+    const f16x4* po = reinterpret_cast<const f16x4*>(p.part_o) + (ws * p.tiles_rg + w) * KQ * 64 + k * 64 + lane;
+    const float2* pm = p.part_ml + ws * p.rows_rg + 32 * w + r32;
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      ml[u] = u < cnt ? pm[(size_t)(q0 + u) * ml_stride] : make_float2(-__builtin_inff(), 0.f);
-      v[u] = u < cnt ? po[(size_t)(q0 + u) * o_stride] : f16x4{};
+      ml[u] = u < cnt ? pm[(size_t)u * ml_stride] : make_float2(-__builtin_inff(), 0.f);
+      v[u] = u < cnt ? po[(size_t)u * o_stride] : f16x4{};
     }
+  };
+  auto combine = [&](int cnt) __attribute__((always_inline)) {
     float mc = M;
 #pragma unroll
-    for (int u = 0; u < kChunk; ++u) mc = fmaxf(mc, ml[u].x);
+    for (int u = 0; u < kChunk; ++u) mc = fmaxf(mc, u < cnt ? ml[u].x : -__builtin_inff());
     const float sc = M == -__builtin_inff() ? 0.f : exp2f(M - mc);
     lsum *= sc;
     acc.x *= sc; acc.y *= sc; acc.z *= sc; acc.w *= sc;
 #pragma unroll
     for (int u = 0; u < kChunk; ++u) {
-      const float wu = u < cnt ? exp2f(ml[u].x - mc) : 0.f;
-      lsum = fmaf(wu, ml[u].y, lsum);
-      acc.x = fmaf(wu, (float)v[u][0], acc.x);
-      acc.y = fmaf(wu, (float)v[u][1], acc.y);
-      acc.z = fmaf(wu, (float)v[u][2], acc.z);
-      acc.w = fmaf(wu, (float)v[u][3], acc.w);
+      const bool in = u < cnt;  // a slot past the pieces may hold anything
+      const float wu = in ? exp2f(ml[u].x - mc) : 0.f;
+      const f16x4 x = in ? v[u] : f16x4{};
+      lsum = fmaf(wu, in ? ml[u].y : 0.f, lsum);
+      acc.x = fmaf(wu, (float)x[0], acc.x);
+      acc.y = fmaf(wu, (float)x[1], acc.y);
+      acc.z = fmaf(wu, (float)x[2], acc.z);
+      acc.w = fmaf(wu, (float)x[3], acc.w);
     }
     M = mc;
+  };
+  if (p.batch == 1) load(0, min(kChunk, p.slots_per_g));
+  const int count = __builtin_amdgcn_readfirstlane(pl.x), first = __builtin_amdgcn_readfirstlane(pl.y);
+  if (count <= 1) return;
+  if (p.batch != 1) load(first, min(kChunk, count));
+  combine(min(kChunk, count));
+  for (int q0 = kChunk; q0 < count; q0 += kChunk) {
+    const int cnt = min(kChunk, count - q0);
+    load(first + q0, cnt);
+    combine(cnt);
   }
+  if (!live) return;
+  const int node = row / p.group;
+  const size_t out_row = ((size_t)b * p.n + node) * p.hq + (size_t)g * p.group + (row - node * p.group);
+  const int d0 = 32 * (k >> 2) + 8 * (k & 3) + 4 * h;
   const float inv = 1.f / lsum;
   typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
   const bf16x4 o = {(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv), (__bf16)(acc.w * inv)};
@@ -172,11 +187,34 @@ __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
 
 }  // namespace
 
+// Pieces taken in one round of loads: enough for every piece of a sequence
+// where the plan gives at most 24 to sequences that fill the capacity, and no
+// more, since a thread's registers bound the loads in flight on the chip.
+// Calls of the attention at 28/4 heads: 64 rows over 4096 keys of 128 dims, 22
+// pieces: 20.0 us with 16, 18.8 with 24, 20.0 with 32; 37 rows of 64 dims,
+// about 10 pieces: 24.8 with 16, 25.3 with 24 and 32.
+static int merge_chunk(const AttnParams& p) {
+  const long tiles = ((long)p.cap + 63) / 64 + 1;
+  long t = (tiles * p.batch + p.slots_per_g - 1) / p.slots_per_g;
+  if (t < p.min_tiles) t = p.min_tiles;
+  const long pieces = (tiles + t - 1) / t;
+  return pieces <= 8 ? 8 : pieces <= 16 || pieces > 24 ? 16 : 24;
+}
+
+template <int D>
+static void launch_pieces(const AttnParams& p, dim3 grid, dim3 block, hipStream_t s) {
+  switch (merge_chunk(p)) {
+    case 8: hipLaunchKernelGGL((attn_merge_pieces<D, 8>), grid, block, 0, s, p); break;
+    case 24: hipLaunchKernelGGL((attn_merge_pieces<D, 24>), grid, block, 0, s, p); break;
+    default: hipLaunchKernelGGL((attn_merge_pieces<D, 16>), grid, block, 0, s, p); break;
+  }
+}
+
 hipError_t launch_attn_merge_pieces(const AttnParams& p, hipStream_t s) {
   const long units = (long)p.batch * p.hkv * p.row_groups * p.tiles_rg;
   const dim3 grid((unsigned)(units * (p.d / 8) / 4)), block(256);
-  if (p.d == 128) hipLaunchKernelGGL((attn_merge_pieces<128>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((attn_merge_pieces<64>), grid, block, 0, s, p);
+  if (p.d == 128) launch_pieces<128>(p, grid, block, s);
+  else launch_pieces<64>(p, grid, block, s);
   return hipGetLastError();
 }
 

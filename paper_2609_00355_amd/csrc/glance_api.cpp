@@ -140,7 +140,10 @@ glance_status make_plan(const glance_attn_shape* s, Plan* out) {
     p.rows_rg = 32 * p.tiles_rg;
     const int per_g = 256 / (p.hkv * p.row_groups);
     p.slots_per_g = per_g > p.batch ? per_g : p.batch;
-    p.min_tiles = 4;
+    // 3 tiles: one 64-row verify (28/4 heads of 128) over 4096 keys took 19.9
+    // us with 2 or 3, 21.5 with 4, 22.6 with 6; a 16-row draft over 2048 keys
+    // 14.0 with 2, 13.5 with 3, 14.2 with 4
+    p.min_tiles = 3;
     const size_t wslots = (size_t)p.slots_per_g * p.hkv * p.row_groups;
     pl.counter_bytes = round_up((size_t)p.batch * sizeof(int2), 256);
     pl.part_ml_bytes = round_up(wslots * p.rows_rg * sizeof(float2), 256);
