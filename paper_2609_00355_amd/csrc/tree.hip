@@ -20,18 +20,15 @@
 //              rows: every value it leaves out lies below thr.  Candidates go
 //              to the slice's own slots (no atomics).
 // tree_rank    one workgroup per row: the log-normaliser from the slice
-//              statistics; the row threshold tau from the sketch (entry i goes
-//              to bucket i mod B and tau is the smallest of the buckets' j-th
-//              largest entries, B * j >= K; the entries are maxima of disjoint
-//              lane groups, so at least K values of the row are >= tau and the
-//              K best all are); the candidates >= tau gathered and ranked by
-//              counting.  A slice whose thr lies above the K-th kept value
-//              may have left one of the K best out, and a slice whose slots
-//              overflowed lost some: those slices are read again for their
-//              values >= tau and the candidates ranked again.  Only if that
-//              overflows too is the K-th largest key of the row found by radix
-//              selection over the whole row.  The row's K best (log q, token)
-//              are written in rank order.
+//              statistics; the row threshold tau, the K-th largest entry of the
+//              sketch (its entries are maxima of disjoint lane groups, so at
+//              least K values of the row are >= tau and the K best all are);
+//              the candidates >= tau gathered and ranked by counting.  A slice
+//              whose thr lies above tau may have left out values >= tau, and a
+//              slice whose slots overflowed lost some: those slices are read
+//              again.  Only if too many candidates are found is the K-th
+//              largest key of the row found by radix selection over the whole
+//              row.  The row's K best (log q, token) are written in rank order.
 // tree_enum    one wave per sequence: the best-first enumeration.  Lane i is
 //              node i; the frontier holds each emitted node's next unemitted
 //              child (its children leave in rank order), kept in the node's
@@ -359,62 +356,15 @@ constexpr int kRescanCap = 64;  // slices re-read by the ranking pass before the
 
 struct RankShared {
   __attribute__((aligned(16))) u64 cand[kTreeCap + 32];
-  u64 top[64];
+  __attribute__((aligned(16))) float ent[kThreads];  // the row's sketch
+  __attribute__((aligned(16))) u64 top[64];          // the exact fallback's result
   int hist[256];
-  float red[8];
-  int iscan[4];
+  float red[12];
   int n, digit, above;
-  float tau;
   int nres;
   int res[kRescanCap];
+  int part[kThreads];
 };
-
-// Block-wide reductions of the 256-thread workgroup (every thread gets the result).
-__device__ __forceinline__ float block_max(float v, RankShared& sh) {
-  v = wave_max_f(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
-}
-// Two maxima at once (one pair of barriers).
-__device__ __forceinline__ void block_max2(float& a, float& b, RankShared& sh) {
-  a = wave_max_f(a);
-  b = wave_max_f(b);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    sh.red[threadIdx.x >> 6] = a;
-    sh.red[4 + (threadIdx.x >> 6)] = b;
-  }
-  __syncthreads();
-  a = fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
-  b = fmaxf(fmaxf(sh.red[4], sh.red[5]), fmaxf(sh.red[6], sh.red[7]));
-}
-__device__ __forceinline__ float block_sum(float v, RankShared& sh) {
-  v = wave_sum_f(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh.red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (sh.red[0] + sh.red[1]) + (sh.red[2] + sh.red[3]);
-}
-
-// Exclusive prefix sum over the workgroup in thread order; *total gets the sum.
-__device__ __forceinline__ int block_excl_scan(int v, int* total, RankShared& sh) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int t = __shfl_up(incl, off);
-    if (lane >= off) incl += t;
-  }
-  __syncthreads();
-  if (lane == 63) sh.iscan[wave] = incl;
-  __syncthreads();
-  int before = 0;
-  for (int w = 0; w < wave; ++w) before += sh.iscan[w];
-  *total = sh.iscan[0] + sh.iscan[1] + sh.iscan[2] + sh.iscan[3];
-  return before + incl - v;
-}
 
 // Exact top-K of a whole row when its candidates overflow the ranking: radix
 // selection of the K-th largest packed word, 8 bits per pass from the top,
@@ -621,7 +571,7 @@ __device__ void enumerate(const TreeParams& p, int b, int lane) {
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
   __shared__ RankShared sh;
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const char* rowp = row_ptr(p, row, BF16 ? 2 : 4);
   if (tid == 0) {
     sh.n = 0;
@@ -632,19 +582,18 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
   const int* cnt = p.ccount + (size_t)row * p.slices;
   const int S = p.slices * p.groups;
   const float* sk = p.sketch + (size_t)row * S;
-  float* stage = reinterpret_cast<float*>(sh.cand);  // free until the gather
-  const bool staged = S <= 2 * kTreeCap;
+  const bool counted = S <= kThreads;
 
   // Every first read in flight at once, one slice per thread (further slices
   // of very long rows in the loops below): the slice's statistics, threshold,
   // candidate count and first 16 candidate slots (slots past the count stay
-  // inside the slice's slots and are ignored), and the sketch, staged in LDS
-  // for the bucket scans.
+  // inside the slice's slots and are ignored), and the thread's sketch entry.
   const bool in0 = tid < p.slices;
   const float2 st0 = in0 ? st[tid] : make_float2(-kInf, 0.f);
   const float th0 = in0 ? th[tid] : -kInf;
   const int c0 = in0 ? cnt[tid] : 0;
-  u64 ka[16];  // the first 16 slots (a slice holds 8.5 candidates on average)
+  const float ent0 = counted && tid < S ? sk[tid] : -kInf;
+  u64 ka[16], kb[16];  // slots 0..15 and 16..31 (a slice holds 8.5 candidates on average)
   auto load16 = [&](u64 (&kk)[16], int sl, int j0) {
     const u64* src = p.cand + ((size_t)row * p.slices + sl) * kTreeSliceCap + j0;
 #pragma unroll
@@ -655,37 +604,49 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
     }
   };
   load16(ka, in0 ? tid : 0, 0);
-  if (staged)
-    for (int i = tid; i < S; i += kThreads) stage[i] = sk[i];
-  float M = st0.x, T = th0;
-  for (int i = tid + kThreads; i < p.slices; i += kThreads) {
-    M = fmaxf(M, st[i].x);
-    T = fmaxf(T, th[i]);
-  }
-  __syncthreads();
-  // The row's threshold tau (wave 0): lane l < tau_buckets keeps the
-  // tau_rank largest entries of bucket l (sketch entries l, l + tau_buckets,
-  // ...); tau is the smallest of the buckets' tau_rank-th largest entries.
-  // The sketch entries are maxima of disjoint lane groups, so each bucket
-  // holds tau_rank distinct values >= tau: at least K values of the row are
-  // >= tau, and the K best all are.
-  if (tid < 64) {
-    float t0 = -kInf, t1 = -kInf, t2 = -kInf, t3 = -kInf;
-    if (tid < p.tau_buckets) {
-      for (int i = tid; i < S; i += p.tau_buckets) {
-        float x = staged ? stage[i] : sk[i], h;
-        h = fmaxf(t0, x); x = fminf(t0, x); t0 = h;
-        h = fmaxf(t1, x); x = fminf(t1, x); t1 = h;
-        h = fmaxf(t2, x); x = fminf(t2, x); t2 = h;
-        t3 = fmaxf(t3, x);
-      }
+
+  // The row's maximum M and threshold tau: at least K values of the row are >=
+  // tau and the K best all are, since the sketch entries are maxima of
+  // disjoint lane groups.  Up to 256 entries: tau is their K-th largest, the
+  // smallest entry with fewer than K larger ones, each thread counting the
+  // entries above its own.  More (rows past 262144 values): lane l < B of wave
+  // 0 keeps the j largest entries of bucket l (entries l, l + B, ...; B j >= K)
+  // and tau is the smallest of the buckets' j-th largest ones.
+  float M, tau_part = kInf;
+  if (counted) {
+    sh.ent[tid] = ent0;
+    if (c0 > 16 && c0 <= kTreeSliceCap) load16(kb, tid, 16);  // in flight through the counting
+    __syncthreads();
+    M = -kInf;
+    int above = 0;
+    for (int i = 0; i < (S + 3) / 4; ++i) {  // entries past S are -inf
+      const float4 x = reinterpret_cast<const float4*>(sh.ent)[i];
+      M = fmaxf(fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)), M);
+      above += (x.x > ent0 ? 1 : 0) + (x.y > ent0 ? 1 : 0) + (x.z > ent0 ? 1 : 0) + (x.w > ent0 ? 1 : 0);
     }
-    const float bj = tid >= p.tau_buckets ? kInf : p.tau_rank == 1 ? t0 : p.tau_rank == 2 ? t1 : p.tau_rank == 3 ? t2 : t3;
-    const float tau = wave_min_f(bj);
-    if (tid == 0) sh.tau = tau;
+    if (tid < S && above < p.k) tau_part = ent0;
+  } else {
+    if (c0 > 16 && c0 <= kTreeSliceCap) load16(kb, tid, 16);
+    M = st0.x;
+    for (int i = tid + kThreads; i < p.slices; i += kThreads) M = fmaxf(M, st[i].x);
+    M = wave_max_f(M);
+    if (lane == 0) sh.red[wave] = M;
+    if (wave == 0) {
+      float t0 = -kInf, t1 = -kInf, t2 = -kInf, t3 = -kInf;
+      if (tid < p.tau_buckets) {
+        for (int i = tid; i < S; i += p.tau_buckets) {
+          float x = sk[i], h;
+          h = fmaxf(t0, x); x = fminf(t0, x); t0 = h;
+          h = fmaxf(t1, x); x = fminf(t1, x); t1 = h;
+          h = fmaxf(t2, x); x = fminf(t2, x); t2 = h;
+          t3 = fmaxf(t3, x);
+        }
+      }
+      if (tid < p.tau_buckets) tau_part = p.tau_rank == 1 ? t0 : p.tau_rank == 2 ? t1 : p.tau_rank == 3 ? t2 : t3;
+    }
+    __syncthreads();
+    M = fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));
   }
-  // the log-normaliser's maximum and the largest slice threshold
-  block_max2(M, T, sh);
   float Z = 0.f;
   if (M != -kInf) {
     if (st0.x != -kInf) Z = st0.y * __builtin_amdgcn_exp2f((st0.x - M) * kLog2e);
@@ -694,7 +655,15 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
       if (s2.x != -kInf) Z += s2.y * __builtin_amdgcn_exp2f((s2.x - M) * kLog2e);
     }
   }
-  Z = block_sum(Z, sh);
+  Z = wave_sum_f(Z);
+  tau_part = wave_min_f(tau_part);
+  if (lane == 0) {
+    sh.red[4 + wave] = Z;
+    sh.red[8 + wave] = tau_part;
+  }
+  __syncthreads();
+  Z = (sh.red[4] + sh.red[5]) + (sh.red[6] + sh.red[7]);
+  const float tau = fminf(fminf(sh.red[8], sh.red[9]), fminf(sh.red[10], sh.red[11]));
   // The sum holds the maximum's own term exp(0) = 1, so log Z >= 0; keeping
   // that under rounding keeps every log q <= 0 and scores non-increasing
   // along each path.
@@ -702,15 +671,10 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
 
   // The slices' candidates >= tau, in any order (they are ranked by
   // counting); one LDS atomic per wave and round, the wave's prefix sum
-  // placing each lane's keys.  A slice whose slots overflowed is re-read
-  // instead.
-  const unsigned tkey = order_key(sh.tau);
-  auto mark = [&](int sl) {
-    const int at = atomicAdd(&sh.nres, 1);
-    if (at < kRescanCap) sh.res[at] = sl;
-  };
-  // one 16-slot round: the keys >= tau go to sh.cand, placed by the wave's
-  // prefix sum with one LDS atomic per wave
+  // placing each lane's keys.  A slice left out only values below its own
+  // threshold, so it is whole unless that lies above tau (about one slice in
+  // 3500 here) or its slots overflowed: those are read again.
+  const unsigned tkey = order_key(tau);
   auto emit = [&](const u64 (&kk)[16], int j0, int c) {
     unsigned pm = 0;
 #pragma unroll
@@ -732,79 +696,33 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
     const int sl = s0 + tid;
     const bool in = sl < p.slices;
     int c = c0;
+    float t = th0, m = st0.x;
     if (s0 > 0) {
       c = in ? cnt[sl] : 0;
+      t = in ? th[sl] : -kInf;
+      m = in ? st[sl].x : -kInf;
       load16(ka, in ? sl : 0, 0);
+      if (c > 16 && c <= kTreeSliceCap) load16(kb, sl, 16);
     }
-    if (c > kTreeSliceCap) {
-      mark(sl);
-      c = 0;
+    const bool has = in && order_key(m) >= tkey;
+    if (has && (c > kTreeSliceCap || order_key(t) > tkey)) {
+      const int at = atomicAdd(&sh.nres, 1);
+      if (at < kRescanCap) sh.res[at] = sl;
     }
-    const int rounds = wave_max_i((c + 15) >> 4);
-    emit(ka, 0, c);
-    for (int r = 1; r < rounds; ++r) {
-      load16(ka, in ? sl : 0, 16 * r);
-      emit(ka, 16 * r, c);
+    if (!has || c > kTreeSliceCap) c = 0;
+    const int most = wave_max_i(c);
+    if (most > 0) emit(ka, 0, c);
+    if (most > 16) emit(kb, 16, c);
+    for (int j0 = 32; j0 < most; j0 += 16) {
+      load16(ka, in ? sl : 0, j0);
+      emit(ka, j0, c);
     }
-  }
-  __syncthreads();
-  // Ranking by counting: the rank of a key is the number of larger keys.
-  // sh.cand is padded with zeros (below every key) to a multiple of 32 and
-  // read 16 bytes at a time, 32 keys per round.
-  auto count_above = [&](u64 key, int n32) {
-    int r = 0;
-    for (int i = 0; i < n32; i += 32) {
-#pragma unroll
-      for (int u = 0; u < 32; u += 2) {
-        const ulonglong2 w = *reinterpret_cast<const ulonglong2*>(&sh.cand[i + u]);
-        r += (w.x > key ? 1 : 0) + (w.y > key ? 1 : 0);
-      }
-    }
-    return r;
-  };
-  auto pad = [&](int n) {
-    for (int i = n + tid; i < ((n + 31) & ~31); i += kThreads) sh.cand[i] = 0;
-    __syncthreads();
-    return (n + 31) & ~31;
-  };
-  // sh.top[r] = the candidate of rank r < K (needs K <= n <= kTreeCap); with
-  // n <= kThreads each thread keeps its own candidate's rank
-  int my_rank = 0;
-  u64 my_key = 0;
-  auto rank_all = [&]() {
-    const int n = sh.n, n32 = pad(n);
-    for (int t = tid; t < n; t += kThreads) {
-      const u64 key = sh.cand[t];
-      const int rank = count_above(key, n32);
-      if (rank < p.k) sh.top[rank] = key;
-      my_rank = rank;
-      my_key = key;
-    }
-    __syncthreads();
-  };
-  const int n0 = sh.n;
-  bool ranked = false;
-  if (n0 >= p.k && n0 <= kTreeCap) {
-    rank_all();
-    ranked = true;
-  }
-  // Every value a slice left out lies below its threshold, so only slices
-  // whose threshold is above the K-th kept value (above tau while fewer than
-  // K are kept) can hide one of the K best: re-read those, adding their
-  // values >= tau that are below the threshold (all of them where the slots
-  // overflowed).  Afterwards every slice either holds all its values >= tau
-  // or left out only values below the K-th kept one, so the ranking is exact.
-  const unsigned vkey = ranked ? (unsigned)(sh.top[p.k - 1] >> 32) : tkey;
-  for (int sl = tid; sl < p.slices; sl += kThreads) {
-    const int c = sl == tid ? c0 : cnt[sl];
-    const float t = sl == tid ? th0 : th[sl];
-    if (c <= kTreeSliceCap && order_key(t) > vkey) mark(sl);
   }
   __syncthreads();
   const int nres = sh.nres;
-  bool exact = ranked && nres == 0;
-  if (nres > 0 && nres <= kRescanCap && n0 <= kTreeCap) {
-    // four consecutive values per thread and slice
+  if (nres > 0 && nres <= kRescanCap) {  // the same in every thread: nres no longer changes (sh.n does)
+    // four consecutive values per thread and slice: those >= tau that are
+    // below the slice's threshold (all of them where the slots overflowed)
     constexpr int kPer = kTreeSlice / kThreads;
     for (int i = 0; i < nres; ++i) {
       const int sl = sh.res[i];
@@ -840,40 +758,55 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
       }
     }
     __syncthreads();
-    const int n1 = sh.n;
-    if (n1 >= p.k && n1 <= kTreeCap) {
-      if (ranked && n1 <= kThreads) {
-        // the earlier ranks grow by the new keys above them; the new keys
-        // are ranked against all
-        const int n32 = pad(n1);
-        if (tid < n0) {
-          for (int i = n0; i < n1; ++i) my_rank += sh.cand[i] > my_key ? 1 : 0;
-        } else if (tid < n1) {
-          my_key = sh.cand[tid];
-          my_rank = count_above(my_key, n32);
-        }
-        if (tid < n1 && my_rank < p.k) sh.top[my_rank] = my_key;
-        __syncthreads();
-      } else {
-        rank_all();
-      }
-      exact = true;
-    }
   }
-  if (!exact) {
+  // The K best in rank order, in the layout the enumeration reads: slot r
+  // holds the token of rank r and the log q of rank r + 1 (-inf past the
+  // K-th), slot 63 the log q of rank 0.
+  auto write = [&](int rank, u64 key) {
+    const float lq = lse == -kInf ? -kInf : key_value((unsigned)(key >> 32)) - lse;
+    p.tok[(size_t)row * 64 + rank] = (int)(0xffffffffu - (unsigned)key);
+    p.lq[(size_t)row * 64 + (rank == 0 ? 63 : rank - 1)] = lq;
+    if (rank == p.k - 1) p.lq[(size_t)row * 64 + rank] = -kInf;
+  };
+  const int n = sh.n;
+  if (n < p.k || n > kTreeCap || nres > kRescanCap) {
     radix_top<BF16>(p, rowp, sh);
     __syncthreads();
+    if (tid < p.k) write(tid, sh.top[tid]);
+    return;
   }
-  // in the layout the enumeration reads: slot r holds the token of rank r and
-  // the log q of rank r + 1 (-inf past the K-th), slot 63 the log q of rank 0
-  auto log_q = [&](int r) {
-    return lse == -kInf ? -kInf : key_value((unsigned)(sh.top[r] >> 32)) - lse;
+  // Ranking by counting: the rank of a key is the number of larger keys.
+  // sh.cand is padded with zeros (below every key) to a multiple of 64 and
+  // read 16 bytes at a time; up to 128 keys, two threads share a key.
+  const int n64 = (n + 63) & ~63;
+  for (int i = n + tid; i < n64; i += kThreads) sh.cand[i] = 0;
+  __syncthreads();
+  auto count_above = [&](u64 key, int i0, int i1) {
+    int r = 0;
+    for (int i = i0; i < i1; i += 32) {
+#pragma unroll
+      for (int u = 0; u < 32; u += 2) {
+        const ulonglong2 w = *reinterpret_cast<const ulonglong2*>(&sh.cand[i + u]);
+        r += (w.x > key ? 1 : 0) + (w.y > key ? 1 : 0);
+      }
+    }
+    return r;
   };
-  if (tid < p.k) {
-    p.lq[(size_t)row * 64 + tid] = tid + 1 < p.k ? log_q(tid + 1) : -kInf;
-    p.tok[(size_t)row * 64 + tid] = (int)(0xffffffffu - (unsigned)sh.top[tid]);
+  if (n <= 128) {
+    const int at = tid & 127, half = tid >> 7;
+    const u64 key = sh.cand[at < n ? at : 0];
+    const int mine = count_above(key, half * (n64 / 2), (half + 1) * (n64 / 2));
+    if (half) sh.part[at] = mine;
+    __syncthreads();
+    const int rank = mine + sh.part[at];
+    if (!half && at < n && rank < p.k) write(rank, key);
+    return;
   }
-  if (tid == 63) p.lq[(size_t)row * 64 + 63] = log_q(0);
+  for (int t = tid; t < n; t += kThreads) {
+    const u64 key = sh.cand[t];
+    const int rank = count_above(key, 0, n64);
+    if (rank < p.k) write(rank, key);
+  }
 }
 
 __global__ __launch_bounds__(64) void tree_enum(TreeParams p) { enumerate(p, blockIdx.x, threadIdx.x); }
