@@ -18,7 +18,8 @@
 // into LDS (global_load_lds, 16 bytes per lane, no register staging), each
 // its share of every tile, through rings of four K stages and four V stages;
 // one LDS barrier per tile orders the loads and the reads (the ring's rule
-// is stated at ring_wait).
+// is stated at ring_issue; with 64-dim heads all waves load, through
+// registers).
 //
 // Per tile a computing wave runs, for its 32 rows and the tile's 64 keys,
 //   S^T[key][row] = K[key][:] . Q[row][:]           (v_mfma_f32_32x32x16_bf16, A = K, B = Q^T)
@@ -122,8 +123,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 // which would drain the ring.)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <int D, bool TREE>
+// WIDE: five to seven computing waves (tiles_rg > 4), all eight waves load.
+template <int D, bool TREE, bool WIDE>
 __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
+  constexpr bool STAGED = WIDE && D == 64;  // loads by way of registers (see the ring rule)
   using G_ = Geo<D>;
   constexpr int RB = G_::RB, CH = G_::CH, TB = G_::TB, KS = G_::KS, DB = G_::DB;
   constexpr int RPL = G_::RPL, NB = G_::NB, OV = G_::OV;
@@ -167,29 +170,19 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   const char* vc = static_cast<const char*>(p.v_ctx);
   const char* kn = static_cast<const char*>(p.k_new);
   const char* vn = static_cast<const char*>(p.v_new);
-  // This wave's loads of a K (or V) tile: r = first + stride i, i < per_side.
-  constexpr int kMaxLoads = NB / 4;
-  int first, stride, per_side;
-  if (p.tiles_rg <= 4) {
-    first = wave - 4;
-    stride = 4;
-    per_side = wave >= 4 ? NB / 4 : 0;
-  } else {
-    first = wave;
-    stride = 8;
-    per_side = NB / 8;
-  }
+  // This wave's loads of a K (or V) tile: r = first + stride i, i < kLoads.
+  constexpr int kLoads = WIDE ? NB / 8 : NB / 4;
+  constexpr int stride = WIDE ? 8 : 4;
+  const int first = WIDE ? wave : wave - 4;
+  const bool loads = WIDE || wave >= 4;
   // Load r (0 <= r < NB) of a tile fills LDS rows r RPL .. r RPL + RPL - 1;
   // lane i writes row r RPL + i / CH, chunk slot i % CH, which holds the
   // row's chunk slot ^ swz(row).  The lane's row and its byte offset within
-  // a full context tile (row stride RB) are computed once per load slot.
-  int lrow[kMaxLoads];
-  unsigned lchunk[kMaxLoads];
-#pragma unroll
-  for (int i = 0; i < kMaxLoads; ++i) {
-    lrow[i] = (first + stride * i) * RPL + lane / CH;
-    lchunk[i] = (unsigned)(((lane % CH) ^ swz<D>(lrow[i])) * 16);
-  }
+  // a full context tile (row stride RB) are computed once.
+  constexpr int kStep = stride * RPL;  // rows between a wave's loads, a multiple of 16: the same chunk order
+  static_assert(kStep % 16 == 0, "swz has period 16");
+  const int lrow = first * RPL + lane / CH;
+  const unsigned lchunk = (unsigned)(((lane % CH) ^ swz<D>(lrow)) * 16);
   auto issue = [&](int t, bool v_side) __attribute__((always_inline)) {
     const char* gfull = v_side ? vc : kc;
     const unsigned lds = (unsigned)(size_t)(v_side ? sV : sK) + (unsigned)(t % kStages) * TB + first * 1024;
@@ -197,8 +190,8 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
     if (j < ct && 64 * j + 64 <= ctx) {  // full context tile: SGPR base + fixed lane offsets
       const char* base = gfull + (((size_t)b * p.hkv + g) * p.cap + 64 * (size_t)j) * RB;
 #pragma unroll
-      for (int i = 0; i < kMaxLoads; ++i)
-        if (i < per_side) dma16(base, (unsigned)(lrow[i] * RB) + lchunk[i], lds + stride * i * 1024);
+      for (int i = 0; i < kLoads; ++i)
+        dma16(base + i * kStep * RB, (unsigned)(lrow * RB) + lchunk, lds + stride * i * 1024);
       return;
     }
     // ragged context tile or the new keys: rows past the valid ones re-read
@@ -216,31 +209,30 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
       nvalid = p.n;
     }
 #pragma unroll
-    for (int i = 0; i < kMaxLoads; ++i) {
-      if (i < per_side) {
-        const int src = lrow[i] < nvalid ? lrow[i] : nvalid - 1;
-        dma16(base, (unsigned)src * rstride + lchunk[i], lds + stride * i * 1024);
-      }
+    for (int i = 0; i < kLoads; ++i) {
+      const int src = min(lrow + i * kStep, nvalid - 1);
+      dma16(base, (unsigned)src * rstride + lchunk, lds + stride * i * 1024);
     }
   };
   // Ring rule.  Tile t is read by the computing waves' matrix phases: K(t) in
   // X_t, V(t) in X_{t+1} (see the schedule below); X_{t-1} ends before barrier
   // t in every wave.  So right after barrier t the stages of K(t - 1) and
-  // V(t - 2) are free, and before barrier t + 1 each wave issues its share of
-  // K(t + 3) and V(t + 2) into them (group t; the prologue issues groups -3,
-  // -2, -1: K(0), then K(1) V(0), then K(2) V(1)).  Barrier t needs K(t) and
-  // V(t - 1), both of group t - 3, so before it each wave waits until at most
-  // its groups t - 2 and t - 1 are in flight (vmcnt counts this wave's loads,
-  // in issue order): 2 per_side loads a group, so 4 per_side.  Every wave
-  // issues its share of every group: a share left out leaves stale rows in
-  // the stage, which the computing waves then read as tile data.
+  // V(t - 2) are free, and those of K(t - 2) and V(t - 3) have been since
+  // barrier t - 1.  Every wave that loads brings its share of every tile: a
+  // share left out leaves stale rows in the stage, which the computing waves
+  // then read as tile data.
+  //
+  // By DMA: before barrier t + 1 a wave issues its share of
+  // K(t + 3) and V(t + 2) into the stages of K(t - 1) and V(t - 2) (group t;
+  // the prologue issues groups -3, -2, -1: K(0), then K(1) V(0), then K(2)
+  // V(1)).  Barrier t needs K(t) and V(t - 1), both of group t - 3, so before
+  // it the wave waits until at most its groups t - 2 and t - 1 are in flight
+  // (vmcnt counts a wave's loads in issue order; 2 kLoads a group).
   auto ring_issue = [&](int t) __attribute__((always_inline)) {
-    if (per_side == 0) return;
     if (t + 3 < n_tiles) issue(t + 3, false);
     if (t + 2 < n_tiles) issue(t + 2, true);
   };
   auto ring_prologue = [&]() __attribute__((always_inline)) {
-    if (per_side == 0) return;
     issue(0, false);                    // group -3: K(0)
     if (n_tiles > 1) issue(1, false);   // group -2: K(1), V(0)
     issue(0, true);
@@ -248,20 +240,88 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
     if (n_tiles > 1) issue(1, true);
   };
   auto ring_wait = [&](int t) __attribute__((always_inline)) {
-    if (per_side == 0) return;
     if (t + 2 >= n_tiles) wait_vmcnt<0>();
-    else if (per_side == NB / 4) wait_vmcnt<NB>();  // 4 per_side
-    else wait_vmcnt<NB / 2>();                      // per_side = NB / 8
+    else wait_vmcnt<4 * kLoads>();
   };
+
+  // Staged (64-dim heads): the prologue brings K(0), K(1) and V(0) by DMA and
+  // loads K(2), V(1) and K(3), V(2) into two sets of registers; halfway through
+  // step t a wave writes the set of t's parity, its share of K(t + 2) and
+  // V(t + 1), to the stages of K(t - 2) and V(t - 3), and loads K(t + 4) and
+  // V(t + 3) into it.  The tile after barrier t + 1 finds them there, and a
+  // load has two steps to arrive in.  Loads and stores past the last tile are
+  // not left out but repeat it (into stages that nobody reads again): with a
+  // condition on them the compiler's wait for one set would be a wait for
+  // both.  An ordinary load leaves its wave as soon as it is queued, while a
+  // DMA one holds it until the memory pipeline takes it: 37 rows, 28/4 heads of
+  // 64, 3 ragged sequences of 1037 to 11003 keys take 24.1 us instead of 24.9.
+  // With 128-dim heads the two sets (32 registers) do not fit beside the
+  // accumulators: 4 x 64 rows over 16384 keys 78.1 us against 74.5 by DMA.
+  u32x4 stK[2][kLoads], stV[2][kLoads];
+  auto stage_load = [&](int t, bool v_side, u32x4 (&r)[kLoads]) __attribute__((always_inline)) {
+    const int j = tb + min(t, n_tiles - 1);
+    const bool is_ctx = j < ct;
+    const char* base = is_ctx ? (v_side ? vc : kc) + (((size_t)b * p.hkv + g) * p.cap + 64 * (size_t)j) * RB
+                              : (v_side ? vn : kn) + ((size_t)b * p.n * p.hkv + g) * RB;
+    const unsigned rstride = is_ctx ? RB : (unsigned)p.hkv * RB;
+    const int nvalid = is_ctx ? min(64, ctx - 64 * j) : p.n;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      r[i] = *reinterpret_cast<const u32x4*>(base + ((unsigned)min(lrow + i * kStep, nvalid - 1) * rstride + lchunk));
+  };
+  auto stage_store = [&](int t, bool v_side, const u32x4 (&r)[kLoads]) __attribute__((always_inline)) {
+    lds_char* dst = (lds_char*)(v_side ? sV : sK) + (t % kStages) * TB + first * 1024 + 16 * lane;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) *(lds_u32x4*)(dst + stride * i * 1024) = r[i];
+  };
+  auto stage_prologue = [&]() __attribute__((always_inline)) {
+    issue(0, false);
+    if (n_tiles > 1) issue(1, false);
+    issue(0, true);
+    stage_load(2, false, stK[0]);
+    stage_load(1, true, stV[0]);
+    stage_load(3, false, stK[1]);
+    stage_load(2, true, stV[1]);
+  };
+  // before barrier 0: K(0)'s share (K(1), V(0) and both sets may be in flight;
+  // they are older than the first set, whose store waits for it before barrier 1)
+  auto stage_wait0 = [&]() __attribute__((always_inline)) {
+    if (n_tiles == 1) wait_vmcnt<0>();
+    else wait_vmcnt<6 * kLoads>();
+  };
+  auto stage_step = [&](int t, auto P_) __attribute__((always_inline)) {
+    constexpr int P = decltype(P_)::value & 1;  // t's parity
+    stage_store(t + 2, false, stK[P]);
+    stage_store(t + 1, true, stV[P]);
+    stage_load(t + 4, false, stK[P]);
+    stage_load(t + 3, true, stV[P]);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
 
   if (wave >= p.tiles_rg) {
     // a wave without rows: streams its share of the tiles and keeps the
     // barrier count
-    ring_prologue();
+    if (STAGED) {
+      stage_prologue();
+      stage_wait0();
+      for (int t = 0;;) {
+        lds_barrier();
+        stage_step(t, I0{});
+        if (++t >= n_tiles) break;
+        lds_barrier();
+        stage_step(t, I1{});
+        if (++t >= n_tiles) break;
+      }
+      return;
+    }
+    if (loads) ring_prologue();
     for (int t = 0; t < n_tiles; ++t) {
-      ring_wait(t);
+      if (loads) ring_wait(t);
       lds_barrier();
-      ring_issue(t);
+      if (loads) ring_issue(t);
     }
     return;
   }
@@ -275,13 +335,11 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   const int hl = row_ok ? row - node * p.group : 0;
   const size_t out_row = ((size_t)b * p.n + node) * p.hq + (size_t)g * p.group + hl;
 
-  // This wave's share of the first three ring groups, then the query of the
-  // lane's row (dims 16 ks + 8 h .. +7: the B operands of Q.K^T) and (wave 0,
-  // tree) the parents, all in flight together.  The query and parents are
-  // ordinary loads issued after the tile loads: a wait the compiler places
-  // for them (it counts only the loads it sees) also covers the older tile
-  // loads, which completes more than it needs but never less.
-  ring_prologue();
+  // The query of the lane's row (dims 16 ks + 8 h .. +7: the B operands of
+  // Q.K^T) and (wave 0, tree) the parents, then this wave's share of the first
+  // tiles.  The compiler's waits for the query count the loads it sees, not
+  // the DMA ones: they cover the tiles issued by DMA too.
+  if (WIDE && !STAGED) ring_prologue();
   bf16x8 qf[KS];
   {
     const __bf16* qp = static_cast<const __bf16*>(p.q) + out_row * D + 8 * h;
@@ -291,7 +349,7 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   const bool tree_words = TREE && has_new && wave == 0;
   int par = -1;
   if (tree_words && lane < p.n) par = p.parents[(size_t)b * p.n + lane];
-  ring_wait(0);
+  if (STAGED) stage_prologue();
   if (tree_words) {
     const unsigned long long anc = ancestor_word(par, lane);
     if (lane < p.n) sAnc[lane] = anc;  // read after the tile barriers
@@ -326,7 +384,7 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
 #pragma unroll
   for (int db = 0; db < DB; ++db) O[db] = f32x16{};
   u32x4 Pw[2][2];  // probabilities as bf16 pairs [key block][16-key k-step]
-  float m_run = kNegInf, l_run = 0.f, nmc = 0.f;
+  float m_run = kNegInf, l_run = 0.f;
   const float c = p.scale_log2;
 
   auto load_k = [&](int ks, int kb, int st) __attribute__((always_inline)) {
@@ -341,7 +399,7 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
 
   // scores (kb, j, i = 0..3) -> probabilities into Pw and their sum (from the
   // same bf16 values that P.V uses, so numerator and denominator match)
-  auto soft_group = [&](int kb, int j, float& lsum) __attribute__((always_inline)) {
+  auto soft_group = [&](int kb, int j, float nmc, float& lsum) __attribute__((always_inline)) {
     const float e0 = __builtin_amdgcn_exp2f(fmaf(S[kb][4 * j + 0], c, nmc));
     const float e1 = __builtin_amdgcn_exp2f(fmaf(S[kb][4 * j + 1], c, nmc));
     const float e2 = __builtin_amdgcn_exp2f(fmaf(S[kb][4 * j + 2], c, nmc));
@@ -368,7 +426,12 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
     const int nvalid = is_new ? p.n : min(64, ctx - 64 * j);
     if (is_new || nvalid < 64) {
       unsigned long long anc = ~0ull;
-      if (TREE && is_new && node < p.n) anc = sAnc[node];
+      if (TREE && is_new) {  // the row's node, worked out here for the same reason as at the end
+        int lane_ = lane;
+        asm volatile("" : "+v"(lane_));
+        const int row_ = 32 * (rgi * p.tiles_rg + wave) + (lane_ & 31);
+        if (row_ < p.rows) anc = sAnc[row_ / p.group];
+      }
       anc >>= 4 * h;
       const int lim = nvalid - 4 * h;
 #pragma unroll
@@ -384,8 +447,9 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
           }
     }
     float lsum = 0.f;
+    float nmc = m_run == kNegInf ? 0.f : -m_run * c;
 #pragma unroll
-    for (int g8 = 0; g8 < 8; ++g8) soft_group(g8 >> 2, g8 & 3, lsum);
+    for (int g8 = 0; g8 < 8; ++g8) soft_group(g8 >> 2, g8 & 3, nmc, lsum);
     if (__builtin_amdgcn_ballot_w64(lsum > kSumLimit || m_run == kNegInf)) {
       float mx = kNegInf;
 #pragma unroll
@@ -403,7 +467,7 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
       for (int db = 0; db < DB; ++db) O[db] *= alpha;
       lsum = 0.f;
 #pragma unroll
-      for (int g8 = 0; g8 < 8; ++g8) soft_group(g8 >> 2, g8 & 3, lsum);
+      for (int g8 = 0; g8 < 8; ++g8) soft_group(g8 >> 2, g8 & 3, nmc, lsum);
     }
     l_run += lsum;
   };
@@ -439,7 +503,10 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
         O[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vr[idx], __builtin_bit_cast(bf16x8, Pw[u >> 1][u & 1]),
                                                         O[db], 0, 0, 0);
       }
-      if (idx == NS / 2 && ti >= 0) ring_issue(ti);
+      if (idx == NS / 2 && ti >= 0) {
+        if (STAGED) stage_step(ti, SK_);
+        else if (WIDE) ring_issue(ti);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
 #if GLANCE_XPRIO
@@ -465,24 +532,22 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   // V(t - 1) before it arrived there.  (Waves 4-6 issue group t halfway
   // through X_t rather than right after barrier t: still between barriers t
   // and t + 1, and X_t reads only K(t) and V(t - 1).)
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
   using YES = std::true_type;
   using NO = std::false_type;
+  if (STAGED) stage_wait0();
+  else if (WIDE) ring_wait(0);
   lds_barrier();  // barrier 0: K(0) has landed, the ancestor words are written
-  ring_issue(0);
-  xphase(I0{}, YES{}, NO{}, -1);
+  if (WIDE && !STAGED) ring_issue(0);
+  xphase(I0{}, YES{}, NO{}, STAGED ? 0 : -1);
   auto step = [&](int t, auto SK_) __attribute__((always_inline)) {
     yphase(t - 1);
-    ring_wait(t);   // this wave's own share of K(t) and V(t - 1) is complete
-    lds_barrier();  // barrier t: every wave's is, and X_{t-1} has ended everywhere
-    // group t: waves 0-3 issue right away, waves 4-6 halfway through X_t, so
-    // that of the two computing waves sharing a SIMD one computes while the
-    // other waits for the memory pipeline to take its loads
-    if (wave < 4) ring_issue(t);
-    xphase(SK_, YES{}, YES{}, wave < 4 ? -1 : t);
+    if (WIDE && !STAGED) ring_wait(t);
+    lds_barrier();  // barrier t: K(t) and V(t - 1) have landed, and X_{t-1} has ended everywhere
+    // DMA by all waves: waves 0-3 issue right away, waves 4-6 halfway through
+    // X_t, so that of the two computing waves sharing a SIMD one computes while
+    // the other waits for the memory pipeline to take its loads
+    if (WIDE && !STAGED && wave < 4) ring_issue(t);
+    xphase(SK_, YES{}, YES{}, STAGED || wave >= 4 ? t : -1);
   };
   int t = 1;
   while (t < n_tiles) {
@@ -506,6 +571,14 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   l_run += __shfl_xor(l_run, 32);  // lanes l and l + 32 hold the same row
   float M = m_run * c;             // reference in log2 units
   float lsum = l_run;
+
+  // the lane's output row, worked out again rather than kept in registers
+  // through the loop
+  int lane_ = lane;
+  asm volatile("" : "+v"(lane_));
+  const int row_ = 32 * (rgi * p.tiles_rg + wave) + (lane_ & 31);
+  const int node_ = row_ / p.group;
+  const size_t out_row_ = ((size_t)b * p.n + node_) * p.hq + (size_t)g * p.group + (row_ - node_ * p.group);
 
   if (split) {
     // Partial of this piece in fp16, in the MFMA layout (four values per lane
@@ -544,9 +617,9 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   }
 
   // output: lane l holds O^T[32 db + 8 j + 4 h + i][row], i = 0..3 consecutive dims
-  if (!row_ok) return;
+  if (row_ >= p.rows) return;
   const float inv = 1.f / lsum;
-  __bf16* op = static_cast<__bf16*>(p.out) + out_row * D + 4 * h;
+  __bf16* op = static_cast<__bf16*>(p.out) + out_row_ * D + 4 * h;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -555,12 +628,18 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
                         (__bf16)(O[db][4 * j + 2] * inv), (__bf16)(O[db][4 * j + 3] * inv)};
       *reinterpret_cast<bf16x4*>(op + 32 * db + 8 * j) = o;
     }
-  if (p.lse && h == 0) p.lse[out_row] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
+  if (p.lse && h == 0) p.lse[out_row_] = (M + __builtin_amdgcn_logf(lsum)) * kLn2;
 }
 
 int grid_blocks(const AttnParams& p) {
   const int slots = p.slots_per_g * p.hkv;
   return ((slots + 7) / 8) * 8 * p.row_groups;
+}
+
+template <int D, bool TREE>
+void launch(const AttnParams& p, dim3 grid, dim3 block, hipStream_t s) {
+  if (p.tiles_rg > 4) hipLaunchKernelGGL((attn_bf16<D, TREE, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((attn_bf16<D, TREE, false>), grid, block, 0, s, p);
 }
 
 }  // namespace
@@ -569,11 +648,11 @@ hipError_t launch_attn_bf16(const AttnParams& p, bool tree, hipStream_t s, hipEv
   const dim3 grid(grid_blocks(p)), block(512);
   if (ev0) (void)hipEventRecord(ev0, s);
   if (p.d == 128) {
-    if (tree) hipLaunchKernelGGL((attn_bf16<128, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_bf16<128, false>), grid, block, 0, s, p);
+    if (tree) launch<128, true>(p, grid, block, s);
+    else launch<128, false>(p, grid, block, s);
   } else {
-    if (tree) hipLaunchKernelGGL((attn_bf16<64, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_bf16<64, false>), grid, block, 0, s, p);
+    if (tree) launch<64, true>(p, grid, block, s);
+    else launch<64, false>(p, grid, block, s);
   }
   hipError_t e = hipGetLastError();
   if (ev1) (void)hipEventRecord(ev1, s);

@@ -177,6 +177,18 @@ def test_many_sequences_more_than_slots():
         _check(kind, w, ctx, n, seed=12, variant="sharp1", poison=True, cap=720, what="40 sequences")
 
 
+# Every length of the tile ring: with 40 sequences for 32 slots per KV head
+# each sequence is one piece, so contexts of 0 .. 8 tiles give pieces of 1 .. 9
+# tiles (whole and ragged last tiles), with all waves loading (24 rows of 7
+# heads are six row tiles) through registers (64 dims) or by DMA (128).
+@pytest.mark.parametrize("d", [64, 128])
+def test_ring_lengths_one_piece_each(d):
+    w = _w("verify_4k", batch=40, d=d)
+    ctx = [min(64 * (i // 5) + (0, 1, 31, 63, 64)[i % 5], 512) for i in range(40)]
+    for kind in ("draft", "verify"):
+        _check(kind, w, ctx, 24, seed=15, variant="sharp1", poison=True, cap=513, what=f"ring d{d}")
+
+
 def test_workspace_reuse_across_shapes():
     """One workspace serves calls of different shapes in turn: every call
     leaves its arrival counters at zero for the next."""
