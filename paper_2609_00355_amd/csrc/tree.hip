@@ -493,15 +493,17 @@ __device__ void enumerate(const TreeParams& p, int b, int lane) {
   int t[kTreeMaxHorizon];
 #pragma unroll
   for (int j = 0; j < kTreeMaxHorizon; ++j) {
-    const bool in = j < L && (lane < K || lane == 63);
-    const size_t at = ((size_t)b * p.horizon + (j < L ? j : 0)) * 64 + lane;
-    q[j] = in ? p.lq[at] : -kInf;
-    t[j] = in && lane < K ? p.tok[at] : 0;
+    // plain loads of every slot (rows past the horizon repeat the last): a
+    // condition would make a branch of each
+    const size_t at = ((size_t)b * L + min(j, L - 1)) * 64 + lane;
+    q[j] = p.lq[at];
+    t[j] = p.tok[at];
   }
 #pragma unroll
   for (int j = 0; j < kTreeMaxHorizon; ++j) {
-    es.ent[j][lane] = make_uint2(lane < K ? as_u32(q[j]) : as_u32(-kInf), (unsigned)t[j]);
-    if (lane == 63) es.first[j] = q[j];
+    const bool in = j < L && lane < K;
+    es.ent[j][lane] = make_uint2(as_u32(in ? q[j] : -kInf), (unsigned)t[j]);
+    if (lane == 63) es.first[j] = j < L ? q[j] : -kInf;
   }
   es.ent[kTreeMaxHorizon][lane] = make_uint2(as_u32(-kInf), 0u);
   if (lane < 2) es.first[kTreeMaxHorizon + lane] = -kInf;
