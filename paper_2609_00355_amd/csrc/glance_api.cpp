@@ -584,8 +584,6 @@ glance_status glance_build_tree(int32_t batch, int32_t horizon, int32_t vocab, i
   p.lq = reinterpret_cast<float*>(ws + pl.off_lq);
   p.tok = reinterpret_cast<int32_t*>(ws + pl.off_tok);
   p.ccount = reinterpret_cast<int32_t*>(ws + pl.off_ccount);
-  p.vec = (reinterpret_cast<uintptr_t>(draft_logits) & 15u) == 0 && ((size_t)vocab * esz) % 16 == 0 &&
-          ((size_t)seq_stride * esz) % 16 == 0;
   hipEvent_t e0, e1;
   take_events(&e0, &e1);
   return check_hip(glance::launch_tree(p, logits_dtype == GLANCE_BF16, stream, e0, e1),

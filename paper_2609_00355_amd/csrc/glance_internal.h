@@ -110,7 +110,6 @@ struct TreeParams {
   int tau_buckets;  // B: threshold buckets over the sketch
   int tau_rank;     // j in 1..4: the bucket entry of rank j bounds the threshold; B * j >= k
   int wgs_per_row;  // ceil(slices / (kTreeScanWaves * kTreeSlicesPerWave))
-  int vec;          // rows are 16-byte aligned: vector loads
 };
 
 // Commit of an accepted path: k_new/v_new [batch][n][hkv][d] rows of the path

@@ -51,6 +51,11 @@ namespace glance {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
+// at any bf16 or fp32 element: rows of any length take vector loads, which
+// the memory pipeline serves unaligned
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
 typedef unsigned long long u64;
 
 constexpr int kThreads = 256;
@@ -162,14 +167,13 @@ __device__ __forceinline__ int slice_pos(int base, int lane, int i) {
 
 // The 16 values of one lane in one slice; positions past the row read -inf.
 template <bool BF16>
-__device__ __forceinline__ void load_slice(const char* rowp, int base, int vocab, int lane, bool vec,
-                                           float (&v)[16]) {
+__device__ __forceinline__ void load_slice(const char* rowp, int base, int vocab, int lane, float (&v)[16]) {
   constexpr int V = SliceShape<BF16>::kVpl;
 #pragma unroll
   for (int l = 0; l < SliceShape<BF16>::kLoads; ++l) {
     const int e0 = slice_pos<BF16>(base, lane, l * V);
-    if (vec && e0 + V <= vocab) {
-      const u32x4 w = *reinterpret_cast<const u32x4*>(rowp + (size_t)e0 * (BF16 ? 2 : 4));
+    if (e0 + V <= vocab) {
+      const u32x4 w = *reinterpret_cast<const u32x4_any*>(rowp + (size_t)e0 * (BF16 ? 2 : 4));
       if (BF16) {
         v[l * 8 + 0] = as_f32(w.x << 16);
         v[l * 8 + 1] = as_f32(w.x & 0xffff0000u);
@@ -192,7 +196,7 @@ __device__ __forceinline__ void load_slice(const char* rowp, int base, int vocab
   }
 }
 
-// The same for a slice wholly inside a 16-byte aligned row: plain vector
+// The same for a slice wholly inside the row: plain vector
 // loads with no per-lane guard (a per-lane guard makes each load a branch of
 // its own, waited on before the next is issued).  Issue first, convert after,
 // so that all of a wave's loads are in flight together.
@@ -202,7 +206,7 @@ __device__ __forceinline__ void issue_slice_full(const char* rowp, int base, int
   constexpr int V = SliceShape<BF16>::kVpl;
 #pragma unroll
   for (int l = 0; l < SliceShape<BF16>::kLoads; ++l)
-    w[l] = *reinterpret_cast<const u32x4*>(rowp + (size_t)slice_pos<BF16>(base, lane, l * V) * (BF16 ? 2 : 4));
+    w[l] = *reinterpret_cast<const u32x4_any*>(rowp + (size_t)slice_pos<BF16>(base, lane, l * V) * (BF16 ? 2 : 4));
 }
 template <bool BF16>
 __device__ __forceinline__ void unpack_slice(const u32x4 (&w)[SliceShape<BF16>::kLoads], float (&v)[16]) {
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(64 * kTreeScanWaves) void tree_scan(TreeParams p) {
   if (s0 >= p.slices) return;
   const char* rowp = row_ptr(p, row, BF16 ? 2 : 4);
   float v[kTreeSlicesPerWave][16];
-  if (p.vec && (s0 + kTreeSlicesPerWave) * kTreeSlice <= p.vocab) {  // uniform: every slice full
+  if ((long)(s0 + kTreeSlicesPerWave) * kTreeSlice <= p.vocab) {  // uniform: every slice full
     u32x4 w[kTreeSlicesPerWave][SliceShape<BF16>::kLoads];
 #pragma unroll
     for (int u = 0; u < kTreeSlicesPerWave; ++u) issue_slice_full<BF16>(rowp, (s0 + u) * kTreeSlice, lane, w[u]);
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(64 * kTreeScanWaves) void tree_scan(TreeParams p) {
   } else {
 #pragma unroll
     for (int u = 0; u < kTreeSlicesPerWave; ++u)
-      if (s0 + u < p.slices) load_slice<BF16>(rowp, (s0 + u) * kTreeSlice, p.vocab, lane, p.vec != 0, v[u]);
+      if (s0 + u < p.slices) load_slice<BF16>(rowp, (s0 + u) * kTreeSlice, p.vocab, lane, v[u]);
 #pragma unroll
     for (int u = 0; u < kTreeSlicesPerWave; ++u)
       if (s0 + u < p.slices) scan_slice<BF16, false>(p, row, s0 + u, lane, v[u]);
@@ -732,19 +736,19 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
       const unsigned hkey = order_key(th[sl]);
       const int e0 = sl * kTreeSlice + kPer * tid;
       float v[kPer];
-      if (p.vec && e0 + kPer <= p.vocab) {
+      if (e0 + kPer <= p.vocab) {
         if (BF16) {
-          const uint2 w = *reinterpret_cast<const uint2*>(rowp + (size_t)e0 * 2);
+          const u32x2 w = *reinterpret_cast<const u32x2_any*>(rowp + (size_t)e0 * 2);
           v[0] = as_f32(w.x << 16);
           v[1] = as_f32(w.x & 0xffff0000u);
           v[2] = as_f32(w.y << 16);
           v[3] = as_f32(w.y & 0xffff0000u);
         } else {
-          const float4 w = *reinterpret_cast<const float4*>(rowp + (size_t)e0 * 4);
-          v[0] = w.x;
-          v[1] = w.y;
-          v[2] = w.z;
-          v[3] = w.w;
+          const u32x4 w = *reinterpret_cast<const u32x4_any*>(rowp + (size_t)e0 * 4);
+          v[0] = as_f32(w.x);
+          v[1] = as_f32(w.y);
+          v[2] = as_f32(w.z);
+          v[3] = as_f32(w.w);
         }
       } else {
 #pragma unroll

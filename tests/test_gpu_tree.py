@@ -316,3 +316,19 @@ def test_repeated_calls_reuse_the_workspace():
     for k in ("parents", "tokens", "scores"):
         assert torch.equal(a1[k], b1[k])
     assert not torch.equal(a1["tokens"], a2["tokens"])
+
+
+# Rows that are no multiple of 16 bytes: every row but the first starts
+# unaligned, slices end inside the row's last vector, and a sequence starts at
+# an odd element (first_row = 1 of an odd vocabulary).
+@pytest.mark.parametrize("vocab", [1023, 1025, 2049 + 5, 50257])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_unaligned_rows(vocab, dtype):
+    w = W.WORKLOADS["verify_4k"]
+    z = W.draft_logits(w, seed=vocab, batch=2, horizon=6, vocab=vocab, dtype=dtype)
+    for b in range(2):
+        z[b, 1 + b, vocab - 1] = z[b, 1 + b].max() + 1  # the best of a row in its last element
+        z[b, 3, 0] = z[b, 3].max() + 1                  # and in its first
+    roots = W.draft_roots(w, seed=3, batch=2, vocab=vocab)
+    out = run_tree(z, roots, 40, first_row=1, horizon=5)
+    check_batch(z[:, 1:], roots, 40, out)
