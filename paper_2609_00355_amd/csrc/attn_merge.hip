@@ -196,7 +196,8 @@ __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
 static int merge_chunk(const AttnParams& p) {
   const long tiles = ((long)p.cap + 63) / 64 + 1;
   long t = (tiles * p.batch + p.slots_per_g - 1) / p.slots_per_g;
-  if (t < p.min_tiles) t = p.min_tiles;
+  const long least = least_piece(p, (int)tiles);
+  if (t < least) t = least;
   const long pieces = (tiles + t - 1) / t;
   return pieces <= 8 ? 8 : pieces <= 16 || pieces > 24 ? 16 : 24;
 }

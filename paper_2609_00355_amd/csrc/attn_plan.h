@@ -71,8 +71,23 @@ __device__ __forceinline__ float log_sum(float M, float sum) {
   return fmaf((float)__builtin_amdgcn_frexp_expf(sum), ln2, fmaf(M, ln2, frac));
 }
 
+// The smallest piece, in tiles, for a longest sequence of `longest` tiles: the
+// merge pass takes up to 24 pieces in one round of loads, and a further round
+// costs it more than another tile costs the attention, up to pieces of seven
+// tiles (four where more than four row tiles make a tile dearer).  Calls with
+// few KV heads, whose pieces are the smallest, with a least piece of 3 tiles,
+// 4, and by this rule: 336 tiles x 2, 4 rows of 4/1 heads of 64: 21.4, 19.5,
+// 16.7 us; 124 x 1, 16 rows of 6/3 heads of 64: 14.4, 13.5, 12.9; 173 x 3, 44
+// rows of 8/1 heads of 128: 25.1, 25.1, 25.1 (26.2 with pieces of seven).
+__host__ __device__ __forceinline__ int least_piece(const AttnParams& p, int longest) {
+  const int most = p.tiles_rg > 4 ? 4 : 7;
+  const int t = (longest + 23) / 24;
+  const int least = t < most ? t : most;
+  return least > p.min_tiles ? least : p.min_tiles;
+}
+
 // The piece plan (identical in every wave of every workgroup): T is the
-// smallest piece size, at least min_tiles, with sum_b ceil(len_b / T) <=
+// smallest piece size, at least least_piece(), with sum_b ceil(len_b / T) <=
 // slots; piece slot ps then names piece ps - first_b of the sequence b with
 // first_b <= ps < first_b + n_b.  Returns false if the slot is unused.  The
 // lengths are read once (sequences lane + 64 k, k < kPlanCache, held in
@@ -116,7 +131,7 @@ __device__ __forceinline__ bool find_piece_in(const AttnParams& p, int ps, int l
     for (int k = 0; k < chunks; ++k) cnt += (len_of(k) + T - 1) / T;
     return wave_sum(cnt);
   };
-  int lo = max(p.min_tiles, (total + slots - 1) / slots);
+  int lo = max(least_piece(p, longest), (total + slots - 1) / slots);
   if (count(lo) > slots) {  // not for equal lengths
     // With T = longest every sequence is one piece (slots >= batch), and with
     // T >= total / (slots - batch) the sum stays below total / T + batch.
