@@ -41,10 +41,11 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
 # a quarter of that rate and counts as 4).
 VALU_PEAK_TOPS = 39.32
 # Work of the sampling walk's row draws per token, in full-rate lane
-# operations: a quarter of one Philox4x32-10 call (20 64-bit multiplies at 4
-# each plus 20 three-input XORs: 100 per four tokens = 25), the noise bound and
-# its test (8), and the load and unpack of a bf16 pair (1).
-SAMPLE_OPS_PER_TOKEN = 34
+# operations: a quarter of what a group of four needs, one Philox4x32-10 call
+# (17 64-bit multiplies at 4 each, the first one an addition and two uniform,
+# plus 16 three-input XORs and that addition's 2: 86), the threshold on its
+# words and the test (12 and one exponential at 4) and the load and unpack (4).
+SAMPLE_OPS_PER_TOKEN = 26.5
 
 
 def parse():
