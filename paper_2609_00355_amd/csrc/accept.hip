@@ -160,18 +160,20 @@ __device__ __forceinline__ void entropy_rebase(float m, float M, float& S, float
 // workgroups stream their chunks.  The whole acceptance at 4 x 64 x 152064
 // bf16: 54.8 us when the root rows' own argmax workgroups (8 of 512) read
 // their chunks a second time value by value, 17.5 us with these (76 more).
-template <bool BF16>
+// Rows of up to 2048 values take a step of that size (4 x 64 x 1150: the
+// 8192-value step's padding cost 0.4 of 7.5 us).
+template <bool BF16, int STEP>
 __device__ __forceinline__ void entropy_chunk(const AcceptParams& p, int b, int chunk) {
   constexpr int V = BF16 ? 8 : 4;  // values per 16-byte load
-  constexpr int LOADS = kEntropyStep / (256 * V);
+  constexpr int LOADS = STEP / (256 * V);
   __shared__ float red_m[4], red_s[4], red_t[4];
   const int tid = threadIdx.x;
   const char* rowp = static_cast<const char*>(p.logits) + (size_t)b * p.n_nodes * p.vocab * (BF16 ? 2 : 4);
   const int begin = chunk * p.ent_len;
   const int end = min(p.vocab, begin + p.ent_len);
   float m = -__builtin_inff(), S = 0.f, T = 0.f;
-  for (int c0 = begin; c0 < end; c0 += kEntropyStep) {
-    const int c1 = min(end, c0 + kEntropyStep);
+  for (int c0 = begin; c0 < end; c0 += STEP) {
+    const int c1 = min(end, c0 + STEP);
     u32x4 w[LOADS];
 #pragma unroll
     for (int l = 0; l < LOADS; ++l) {
@@ -239,7 +241,9 @@ __global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
   // the entropy's workgroups come first, so that they end with the others
   const int ent_blocks = p.root_entropy ? p.batch * p.ent_chunks : 0;
   if ((int)blockIdx.x < ent_blocks) {
-    entropy_chunk<BF16>(p, blockIdx.x / p.ent_chunks, blockIdx.x % p.ent_chunks);
+    const int b = blockIdx.x / p.ent_chunks, c = blockIdx.x % p.ent_chunks;
+    if (p.vocab <= 2048) entropy_chunk<BF16, 2048>(p, b, c);
+    else entropy_chunk<BF16, kEntropyStep>(p, b, c);
     return;
   }
   const int block = blockIdx.x - ent_blocks;

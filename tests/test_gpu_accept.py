@@ -248,7 +248,8 @@ def test_one_workspace_across_calls_and_shapes():
 # take unaligned 16-byte loads with up to 7 values left over: the edges of
 # both, more entropy chunks (66) than the walk has lanes, and a batch whose
 # workspace has room for one chunk a sequence (several steps per workgroup).
-@pytest.mark.parametrize("batch,vocab", [(2, 8191), (2, 8192), (2, 8193), (2, 16391), (2, 65 * 8192 + 9), (410, 20483)])
+@pytest.mark.parametrize("batch,vocab", [(2, 2048), (2, 2049), (2, 8191), (2, 8192), (2, 8193), (2, 16391), (2, 65 * 8192 + 9),
+                                         (410, 20483)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_entropy_and_argmax_at_chunk_edges(batch, vocab, dtype):
     g = torch.Generator().manual_seed(vocab)
