@@ -145,11 +145,13 @@ __device__ __forceinline__ void argmax_bf16_fast(const unsigned short* x, int c0
 }
 
 // (S, T) relative to maximum m, moved to the maximum M >= m:
-// e^(z-M) (z-M) = e^(m-M) e^(z-m) ((z-m) + (m-M)).
+// e^(z-M) (z-M) = e^(m-M) e^(z-m) ((z-m) + (m-M)).  Values so far below M that
+// e^(m-M) is zero leave nothing: masked tokens may hold the type's lowest
+// value, with which (m-M) S overflows.
 __device__ __forceinline__ void entropy_rebase(float m, float M, float& S, float& T) {
   if (S == 0.f) return;  // no mass yet (m may be -inf)
   const float f = __builtin_amdgcn_exp2f((m - M) * 1.4426950408889634f);
-  T = (T + (m - M) * S) * f;
+  T = f == 0.f ? 0.f : (T + (m - M) * S) * f;
   S *= f;
 }
 
@@ -208,7 +210,7 @@ __device__ __forceinline__ void entropy_chunk(const AcceptParams& p, int b, int 
     each([&](float z) __attribute__((always_inline)) {
       const float d = z - m;
       const float x = __builtin_amdgcn_exp2f(d * 1.4426950408889634f);
-      const bool mass = z != -__builtin_inff();  // -inf carries no probability
+      const bool mass = x > 0.f;  // d may be -inf, or NaN while all are -inf
       S += mass ? x : 0.f;
       T += mass ? x * d : 0.f;
     });

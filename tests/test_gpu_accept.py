@@ -270,3 +270,28 @@ def test_entropy_and_argmax_at_chunk_edges(batch, vocab, dtype):
     for b in range(batch):
         ref = OA.row_entropy(logits[b, 0])
         assert abs(float(res["root_entropy"][b]) - ref) <= 2e-4 + 2e-5 * abs(ref)
+
+
+# Vocabularies whose unused tokens hold the lowest finite value of the type
+# (padding, grammar masks): a padded tail that gives some threads nothing else,
+# a step of 2048 values, whole steps and entropy workgroups without mass, and
+# a token that carries all of it.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("batch,vocab,lo,hi", [(2, 2048, 2032, 2048), (2, 1150, 8, 1150), (2, 50304, 50257, 50304),
+                                               (2, 152064, 0, 142064), (8, 152064, 10000, 152064),
+                                               (2, 152064, 1, 152064)])
+def test_root_entropy_with_lowest_finite_masks(dtype, batch, vocab, lo, hi):
+    g = torch.Generator().manual_seed(vocab + lo)
+    n = 3
+    logits = torch.randn((batch, n, vocab), generator=g).to(dtype)
+    logits[:, :, lo:hi] = torch.finfo(dtype).min
+    par = torch.tensor([[-1, 0, 1]] * batch, dtype=torch.int32)
+    am = logits.float().argmax(-1)
+    tok = torch.stack([torch.zeros(batch, dtype=torch.int64), am[:, 0], am[:, 1]], 1).to(torch.int32)
+    res = G.glance_greedy_accept(logits.cuda(), par.cuda(), tok.cuda(), want_entropy=True)
+    got = {k: res[k].cpu().numpy() for k in ("argmax", "accept_len", "accept_path", "next_root")}
+    assert_accept_equal(got, logits, par, tok)
+    h = res["root_entropy"].cpu().numpy()
+    for b in range(batch):
+        ref = OA.row_entropy(logits[b, 0])
+        assert abs(h[b] - ref) <= 2e-4 + 2e-5 * abs(ref), (b, h[b], ref)
