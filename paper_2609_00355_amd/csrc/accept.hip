@@ -208,11 +208,12 @@ __device__ __forceinline__ void entropy_chunk(const AcceptParams& p, int b, int 
     entropy_rebase(m, mc, S, T);
     m = mc;
     each([&](float z) __attribute__((always_inline)) {
-      const float d = z - m;
+      // finite, so that x d is zero with x: z - m is -inf for z = -inf (and may
+      // be for the lowest value), NaN while every value is -inf
+      const float d = fmaxf(z - m, -3.4028234663852886e38f);
       const float x = __builtin_amdgcn_exp2f(d * 1.4426950408889634f);
-      const bool mass = x > 0.f;  // d may be -inf, or NaN while all are -inf
-      S += mass ? x : 0.f;
-      T += mass ? x * d : 0.f;
+      S += x;
+      T += x * d;
     });
   }
   float M = m;
