@@ -285,9 +285,10 @@ __device__ __forceinline__ void scan_slice(const TreeParams& p, int row, int sli
   const float m = key_float(mk), thr = key_float(tk);
   float sum = 0.f;
   if (m != -kInf) {
-    const float mb = m * kLog2e;
+    // the maximum comes off before the scaling: masked tokens may hold the
+    // type's lowest value, which times log2 e overflows
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(v[i], kLog2e, -mb));
+    for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f((v[i] - m) * kLog2e);
   }
   sum = wave_sum_f(sum);
   const size_t sl = (size_t)row * p.slices + slice;

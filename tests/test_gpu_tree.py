@@ -332,3 +332,22 @@ def test_unaligned_rows(vocab, dtype):
     roots = W.draft_roots(w, seed=3, batch=2, vocab=vocab)
     out = run_tree(z, roots, 40, first_row=1, horizon=5)
     check_batch(z[:, 1:], roots, 40, out)
+
+
+# Tokens masked with the lowest finite value of the type: a whole 1024-value
+# slice of it, and rows of which a few tokens in one slice remain (more than
+# the budget, so that every kept string is made of them).
+@pytest.mark.parametrize("vocab,keep", [(4096, None), (50257, None), (5000, 40), (152064, 24)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_rows_masked_with_the_lowest_finite_value(vocab, keep, dtype):
+    w = W.WORKLOADS["verify_4k"]
+    z = W.draft_logits(w, seed=vocab, batch=2, horizon=4, vocab=vocab, dtype=dtype)
+    low = torch.finfo(dtype).min
+    if keep is None:
+        z[:, :, 1024:2048] = low
+    else:
+        z[:, :, : 2048 - keep] = low
+        z[:, :, 2048:] = low
+    roots = W.draft_roots(w, seed=5, batch=2, vocab=vocab)
+    out = run_tree(z, roots, 63 if keep is None else 20)
+    check_batch(z, roots, 63 if keep is None else 20, out)
