@@ -65,7 +65,7 @@ static void attention() {
       CHECK(need == glance_attn_workspace_size(&s, 0));
       for (int tree = 0; tree < 2; ++tree) {
         workspace(need);
-        const int before = g_stub.attn_bf16 + g_stub.attn_f32;
+        const int before = g_stub.attn_bf16 + g_stub.attn_f32, merges = g_stub.merge;
         void* ws = const_cast<void*>(g_stub.ws);
         void* kc = s.ctx_capacity ? fake(2) : nullptr;
         glance_status st = tree ? glance_tree_verify_attn(&s, fake(1), kc, kc ? fake(3) : nullptr, fake(4), fake(5),
@@ -77,6 +77,8 @@ static void attention() {
         CHECK(st == GLANCE_OK);
         CHECK(g_stub.attn_bf16 + g_stub.attn_f32 == before + 1);
         CHECK(g_stub.tree == (tree == 1));
+        // a single split of the fp32 path writes the output itself: no merge
+        CHECK(g_stub.merge == merges + (dt == GLANCE_BF16 || g_stub.nsplit > 1));
         // one byte short: rejected, nothing launched
         st = glance_block_draft_attn(&s, fake(1), kc, kc ? fake(3) : nullptr, fake(4), fake(5),
                                      (const int32_t*)fake(6), fake(8), nullptr, ws, need - 1, nullptr);
@@ -132,7 +134,11 @@ static void profiling_hook() {
 }
 
 static void acceptance() {
-  const int shapes[][3] = {{4, 64, 152064}, {1, 1, 1}, {16, 64, 152064}, {1, 16, 1000}, {7, 33, 5}, {1, 64, 1 << 30}};
+  // the last three batches leave the entropy less room than it has steps, down
+  // to one entry a sequence
+  const int shapes[][3] = {{4, 64, 152064}, {1, 1, 1},         {16, 64, 152064},     {1, 16, 1000},
+                           {7, 33, 5},      {1, 64, 1 << 30},  {1, 1, 8193},         {100, 5, 152064},
+                           {410, 5, 20483}, {4096, 1, 152064}, {30000, 2, 1 << 24}};
   for (auto& sh : shapes)
     for (int dt = 0; dt < 2; ++dt) {
       const size_t need = glance_accept_workspace_size(sh[0], sh[1], sh[2]);
@@ -162,6 +168,7 @@ static void acceptance() {
       CHECK(st == (need <= (size_t(1) << 20) ? GLANCE_OK : GLANCE_ERR_UNSUPPORTED));
       CHECK(g_stub.accept == b2 + (st == GLANCE_OK));
     }
+  CHECK(g_stub.entropy == 2 * (int)(sizeof shapes / sizeof shapes[0]) && g_stub.entropy_steps >= 6);
   const int before = g_stub.accept + g_stub.sample;
   CHECK(glance_accept_workspace_size(0, 1, 1) == 0);
   CHECK(glance_accept_workspace_size(1, 65, 1) == 0);

@@ -52,6 +52,9 @@ hipError_t launch_attn_f32(const AttnParams& p, bool tree, hipStream_t, hipEvent
   in_ws(p.part_ml, slots * sizeof(float2), "(max, sum) partials");
   in_ws(p.part_o, slots * p.d * sizeof(float), "output partials");
   if ((long long)p.nsplit * p.split_keys < p.cap) abort();
+  if ((p.rows_rg != 16 && p.rows_rg != 32) || p.rows_pad != p.row_groups * p.rows_rg || p.rows_pad < p.rows) abort();
+  if (p.split_keys < 16 || p.split_keys % 16) abort();  // a workgroup walks blocks of 16 keys
+  g_stub.nsplit = p.nsplit;
   return hipSuccess;
 }
 
@@ -70,7 +73,17 @@ hipError_t launch_accept(const AcceptParams& p, bool, hipStream_t, hipEvent_t ev
   g_stub.ev0 = ev0;
   g_stub.ev1 = ev1;
   in_ws(p.part, (size_t)p.batch * p.n_nodes * p.chunks * sizeof(unsigned long long), "chunk words");
-  if (p.root_entropy) in_ws(p.ent_part, (size_t)p.batch * p.chunks * sizeof(float4), "entropy chunks");
+  if (p.root_entropy) {
+    // the entropy's workgroups take ent_len values of a root row each, in whole
+    // steps, and write one entry behind the argmax words of the same launch
+    in_ws(p.ent_part, (size_t)p.batch * p.ent_chunks * sizeof(float4), "entropy chunks");
+    if (reinterpret_cast<const char*>(p.ent_part) < reinterpret_cast<const char*>(p.part + (size_t)p.batch * p.n_nodes * p.chunks))
+      abort();
+    if (p.ent_len < kEntropyStep || p.ent_len % kEntropyStep) abort();
+    if ((long long)p.ent_chunks * p.ent_len < p.vocab || (p.ent_chunks - 1LL) * p.ent_len >= p.vocab) abort();
+    ++g_stub.entropy;
+    if (p.ent_len > kEntropyStep) ++g_stub.entropy_steps;
+  }
   if ((long long)p.chunks * p.chunk_len < p.vocab || p.chunk_len % 8) abort();
   return hipSuccess;
 }
