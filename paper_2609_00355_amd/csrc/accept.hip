@@ -62,12 +62,6 @@ __device__ __forceinline__ unsigned long long pack(int key, int idx) {
          (unsigned long long)(0xffffffffu - (unsigned int)idx);
 }
 
-// Inverse of order_key for a non-NaN key: the fp32 bits of the value.
-__device__ __forceinline__ float key_to_float(int key) {
-  const unsigned bits = key >= 0 ? (unsigned)key : 0x80000000u - (unsigned)key;
-  return __builtin_bit_cast(float, bits);
-}
-
 __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsigned long long b) {
   return a > b ? a : b;
 }

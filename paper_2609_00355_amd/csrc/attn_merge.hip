@@ -33,7 +33,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kMergeWaves = 2;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 
-template <int D, bool BF16>
+template <int D>
 __global__ __launch_bounds__(64 * kMergeWaves) void attn_merge_kernel(AttnParams p) {
   constexpr int LPR = D / 4;     // lanes per row
   constexpr int RPW = 64 / LPR;  // rows per wave
@@ -95,18 +95,10 @@ __global__ __launch_bounds__(64 * kMergeWaves) void attn_merge_kernel(AttnParams
   for (int off = LPR / 2; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
   if (!live || nsb == 1) return;  // one split: written by the attention kernel
   const float inv = 1.f / lsum;
-  if (BF16) {
-    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-    const bf16x4 o = {(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv),
-                      (__bf16)(acc.w * inv)};
-    *reinterpret_cast<bf16x4*>(static_cast<__bf16*>(p.out) + (size_t)row * D + 4 * q) = o;
-  } else {
-    *reinterpret_cast<float4*>(static_cast<float*>(p.out) + (size_t)row * D + 4 * q) =
-        float4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
-  }
+  *reinterpret_cast<float4*>(static_cast<float*>(p.out) + (size_t)row * D + 4 * q) =
+      float4{acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
   if (p.lse && q == 0) p.lse[row] = log_sum(M, lsum);
 }
-
 
 template <int D, int kChunk>
 __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
@@ -219,17 +211,12 @@ hipError_t launch_attn_merge_pieces(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_attn_merge(const AttnParams& p, bool out_bf16, hipStream_t s) {
+hipError_t launch_attn_merge(const AttnParams& p, hipStream_t s) {
   const long total = (long)p.batch * p.n * p.hq;
   const long rows_per_wg = (long)kMergeWaves * 64 / (p.d / 4);
   const dim3 grid((unsigned)((total + rows_per_wg - 1) / rows_per_wg)), block(64 * kMergeWaves);
-  if (p.d == 128) {
-    if (out_bf16) hipLaunchKernelGGL((attn_merge_kernel<128, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_merge_kernel<128, false>), grid, block, 0, s, p);
-  } else {
-    if (out_bf16) hipLaunchKernelGGL((attn_merge_kernel<64, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_merge_kernel<64, false>), grid, block, 0, s, p);
-  }
+  if (p.d == 128) hipLaunchKernelGGL(attn_merge_kernel<128>, grid, block, 0, s, p);
+  else hipLaunchKernelGGL(attn_merge_kernel<64>, grid, block, 0, s, p);
   return hipGetLastError();
 }
 

@@ -228,7 +228,7 @@ glance_status attn_common(bool tree, const glance_attn_shape* s, const void* q, 
   if ((st = check_hip(e, "attention kernel launch")) != GLANCE_OK) return st;
   if (s->dtype == GLANCE_F32 && p.nsplit == 1) return ok();  // every workgroup wrote its rows' output
   e = s->dtype == GLANCE_BF16 ? glance::launch_attn_merge_pieces(p, stream)
-                              : glance::launch_attn_merge(p, false, stream);
+                              : glance::launch_attn_merge(p, stream);
   return check_hip(e, "merge kernel launch");
 }
 
@@ -322,19 +322,6 @@ glance_status tree_plan(int32_t batch, int32_t horizon, int32_t vocab, int32_t b
   p.slices = (vocab + glance::kTreeSlice - 1) / glance::kTreeSlice;
   p.groups = 1;
   while ((long long)p.slices * p.groups < p.k && p.groups < 64) p.groups *= 2;
-  // threshold buckets: four entries each when every bucket holds at least
-  // four sketch entries, else one (the sketch has >= k entries)
-  {
-    const long long S = (long long)p.slices * p.groups;
-    const int j = 4, nb = (p.k + j - 1) / j;
-    if (S / nb >= j) {
-      p.tau_buckets = nb;
-      p.tau_rank = j;
-    } else {
-      p.tau_buckets = p.k;
-      p.tau_rank = 1;
-    }
-  }
   p.wgs_per_row = (p.slices + glance::kTreeScanWaves * glance::kTreeSlicesPerWave - 1) /
                   (glance::kTreeScanWaves * glance::kTreeSlicesPerWave);
   TreePlan pl;

@@ -107,8 +107,6 @@ struct TreeParams {
   int k;            // ranked tokens per offset, min(budget, vocab)
   int slices;       // ceil(vocab / kTreeSlice)
   int groups;       // sketch entries per slice, a power of two in 1..64
-  int tau_buckets;  // B: threshold buckets over the sketch
-  int tau_rank;     // j in 1..4: the bucket entry of rank j bounds the threshold; B * j >= k
   int wgs_per_row;  // ceil(slices / (kTreeScanWaves * kTreeSlicesPerWave))
 };
 
@@ -129,7 +127,7 @@ struct CommitParams {
 
 hipError_t launch_attn_bf16(const AttnParams& p, bool tree, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_attn_f32(const AttnParams& p, bool tree, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
-hipError_t launch_attn_merge(const AttnParams& p, bool out_bf16, hipStream_t s);
+hipError_t launch_attn_merge(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_merge_pieces(const AttnParams& p, hipStream_t s);
 hipError_t launch_accept(const AcceptParams& p, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_sample(const AcceptParams& p, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);

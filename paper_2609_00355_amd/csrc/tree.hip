@@ -141,9 +141,6 @@ __device__ __forceinline__ float wave_sum_f(float v) {  // rows not written by a
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int lane_of(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ __forceinline__ float lane_of_f(float v, int l) {
-  return as_f32((unsigned)__builtin_amdgcn_readlane((int)as_u32(v), l));
-}
 
 template <bool BF16>
 __device__ __forceinline__ float load_one(const char* rowp, int e) {
@@ -616,9 +613,10 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
   // tau and the K best all are, since the sketch entries are maxima of
   // disjoint lane groups.  Up to 256 entries: tau is their K-th largest, the
   // smallest entry with fewer than K larger ones, each thread counting the
-  // entries above its own.  More (rows past 262144 values): lane l < B of wave
-  // 0 keeps the j largest entries of bucket l (entries l, l + B, ...; B j >= K)
-  // and tau is the smallest of the buckets' j-th largest ones.
+  // entries above its own.  More (rows past 262144 values): lane l < B = ceil(K / 4)
+  // of wave 0 keeps the four largest entries of bucket l (entries l, l + B, ...:
+  // 16 at least, as K <= 63) and tau is the smallest of the buckets' fourth
+  // largest ones.
   float M, tau_part = kInf;
   if (counted) {
     sh.ent[tid] = ent0;
@@ -639,9 +637,10 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
     M = wave_max_f(M);
     if (lane == 0) sh.red[wave] = M;
     if (wave == 0) {
+      const int buckets = (p.k + 3) / 4;
       float t0 = -kInf, t1 = -kInf, t2 = -kInf, t3 = -kInf;
-      if (tid < p.tau_buckets) {
-        for (int i = tid; i < S; i += p.tau_buckets) {
+      if (tid < buckets) {
+        for (int i = tid; i < S; i += buckets) {
           float x = sk[i], h;
           h = fmaxf(t0, x); x = fminf(t0, x); t0 = h;
           h = fmaxf(t1, x); x = fminf(t1, x); t1 = h;
@@ -649,7 +648,7 @@ __global__ __launch_bounds__(kThreads) void tree_rank(TreeParams p) {
           t3 = fmaxf(t3, x);
         }
       }
-      if (tid < p.tau_buckets) tau_part = p.tau_rank == 1 ? t0 : p.tau_rank == 2 ? t1 : p.tau_rank == 3 ? t2 : t3;
+      if (tid < buckets) tau_part = t3;
     }
     __syncthreads();
     M = fmaxf(fmaxf(sh.red[0], sh.red[1]), fmaxf(sh.red[2], sh.red[3]));

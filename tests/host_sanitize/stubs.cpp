@@ -58,7 +58,7 @@ hipError_t launch_attn_f32(const AttnParams& p, bool tree, hipStream_t, hipEvent
   return hipSuccess;
 }
 
-hipError_t launch_attn_merge(const AttnParams&, bool, hipStream_t) {
+hipError_t launch_attn_merge(const AttnParams&, hipStream_t) {
   ++g_stub.merge;
   return hipSuccess;
 }
