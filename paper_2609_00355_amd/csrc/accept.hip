@@ -613,11 +613,12 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
     ++len;
     entry = lane == len ? v : entry;
   }
+  const int bonus = __builtin_amdgcn_readlane(am, v);  // every lane still active
   int32_t* path = p.accept_path + (long)b * p.path_stride;
   for (int k = lane; k < p.path_stride; k += 64) path[k] = k < 64 ? entry : -1;
   if (lane == 0) {
     p.accept_len[b] = len;
-    p.next_root[b] = __builtin_amdgcn_readlane(am, v);
+    p.next_root[b] = bonus;
   }
   // sampling with a device round counter: every row draw of this call has
   // read it (the draws kernel ran earlier on the stream), so advance it once
