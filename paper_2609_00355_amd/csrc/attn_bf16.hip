@@ -34,8 +34,9 @@
 // running max and sum are per lane (lanes l and l+32 share a row).
 //
 // Merge.  A piece that is its sequence's only one writes the output and LSE.
-// Otherwise each piece writes its unnormalised output (in the MFMA register
-// layout, one float4 per lane per store) and (max, sum) per row to the
+// Otherwise each piece writes its normalised output in fp16 (in the MFMA
+// register layout, four values per lane per store, each row scaled by a power
+// of two) and a (max, sum) pair per row that carries the scales to the
 // workspace, and attn_merge.hip combines the pieces in a second, fully
 // parallel pass; the first piece of each sequence records the sequence's
 // piece count and first slot for it.
@@ -335,10 +336,11 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   const int hl = row_ok ? row - node * p.group : 0;
   const size_t out_row = ((size_t)b * p.n + node) * p.hq + (size_t)g * p.group + hl;
 
-  // The query of the lane's row (dims 16 ks + 8 h .. +7: the B operands of
-  // Q.K^T) and (wave 0, tree) the parents, then this wave's share of the first
-  // tiles.  The compiler's waits for the query count the loads it sees, not
-  // the DMA ones: they cover the tiles issued by DMA too.
+  // This wave's share of the first tiles (by DMA), the query of the lane's row
+  // (dims 16 ks + 8 h .. +7: the B operands of Q.K^T) and (wave 0, tree) the
+  // parents; staged loads follow them.  The compiler's waits for the query
+  // count the loads it sees, not the DMA ones, so they also wait for the tiles
+  // issued by DMA before it.
   if (WIDE && !STAGED) ring_prologue();
   bf16x8 qf[KS];
   {
@@ -522,7 +524,8 @@ __global__ __launch_bounds__(512) void attn_bf16(AttnParams p) {
   // (lower waves X then Y, upper waves Y then X) did worse, since it put a
   // barrier between the phases of every other wave.
   //
-  // Ring invariant: stage s = t % 4 of the ring holds K(t) from its issue
+  // Ring invariant (by DMA; the staged form's order is stated at stage_load):
+  // stage s = t % 4 of the ring holds K(t) from its issue
   // right after barrier t - 3 and V(t) from its issue right after barrier
   // t - 2.  K(t) is read in X_t only (between barriers t and t + 1), V(t) in
   // X_{t+1} only (between barriers t + 1 and t + 2).  The issue right after

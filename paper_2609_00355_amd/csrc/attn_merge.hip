@@ -1,9 +1,10 @@
 // Second pass of split-KV attention: combine the per-split partial results.
 //
-// Each split s of a row left (m_s, l_s, O_s) with m_s the split's running
-// maximum of the scaled scores in log2 units, l_s = sum exp2(score - m_s) and
-// O_s = sum exp2(score - m_s) v (unnormalised).  With M = max_s m_s:
-//   out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s,   lse = (M + log2 L) ln 2
+// Each split s of a row left (m_s, l_s, O_s) with m_s a reference near the
+// split's largest scaled score in log2 units, l_s = sum exp2(score - m_s) and
+// O_s = sum exp2(score - m_s) v, or all three scaled alike (see
+// attn_merge_pieces).  With M = max_s m_s and L = sum_s 2^(m_s - M) l_s:
+//   out = sum_s 2^(m_s - M) O_s / L,   lse = (M + log2 L) ln 2
 //
 // attn_merge_kernel (fp32 attention): D/4 lanes serve one output row, four
 // dims (16 bytes) each, so a wave merges 64/(D/4) rows.  The row index is the
@@ -14,16 +15,20 @@
 // the attention itself.
 //
 // attn_merge_pieces (bf16 attention): the partials are the pieces' MFMA
-// register tiles in fp16, each row scaled by a power of two that the row's
+// register tiles in fp16, O_s / l_s scaled by a power of two that the row's
 // (max, sum) pair carries (lane l of a 32-row tile holds row l % 32 and, in
 // quad k, dims 32 (k / 4) + 8 (k % 4) + 4 (l / 32) .. +3).  A thread owns one
 // (row, four dims) and reads that quad of every piece of its sequence, in
-// piece order, all loads of a chunk of pieces issued before any is used;
-// consecutive threads read consecutive lanes, 512 bytes per wave-wide load.
-// Sequences with one piece were written by the attention kernel and are
-// skipped.  Bound by latency (two memory round trips after the launch): the
-// only sequence of a batch of one starts at slot 0, so its first chunk's loads
-// go out beside the plan's, before the piece count is known.
+// piece order, a chunk of pieces at a time; consecutive threads read
+// consecutive lanes, 512 bytes per wave-wide load.  Sequences with one piece
+// were written by the attention kernel and are skipped.  Bound by latency.
+// The plan's read is one memory round trip; the only sequence of a batch of
+// one starts at slot 0, so its first chunk's loads go out beside it, before
+// the piece count is known.  A chunk costs more than one round trip: its loads
+// depend on the piece count and so become a branch a piece, between the first
+// of which the compiler puts a wait for the loads before (seen in the
+// assembly after the first two pieces; 16 and 24 pieces also spill 23 and 79
+// scalar registers).
 #include "attn_plan.h"
 
 namespace glance {
@@ -125,7 +130,7 @@ __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
   float2 ml[kChunk];
   f16x4 v[kChunk];
   // the (max, sum) pairs and output quads of up to `cnt` pieces from slot
-  // `slot` on, all loads issued before any is used
+  // `slot` on
   auto load = [&](int slot, int cnt) __attribute__((always_inline)) {
     const size_t ws = ((size_t)g * p.slots_per_g + slot) * p.row_groups + rgi;  // piece u: ws + u * row_groups
     const f16x4* po = reinterpret_cast<const f16x4*>(p.part_o) + (ws * p.tiles_rg + w) * KQ * 64 + k * 64 + lane;
@@ -179,7 +184,7 @@ __global__ __launch_bounds__(256) void attn_merge_pieces(AttnParams p) {
 
 }  // namespace
 
-// Pieces taken in one round of loads: enough for every piece of a sequence
+// Pieces in a chunk of loads: enough for every piece of a sequence
 // where the plan gives at most 24 to sequences that fill the capacity, and no
 // more, since a thread's registers bound the loads in flight on the chip.
 // Calls of the attention at 28/4 heads: 64 rows over 4096 keys of 128 dims, 22

@@ -72,7 +72,7 @@ __device__ __forceinline__ float log_sum(float M, float sum) {
 }
 
 // The smallest piece, in tiles, for a longest sequence of `longest` tiles: the
-// merge pass takes up to 24 pieces in one round of loads, and a further round
+// merge pass takes up to 24 pieces in one chunk of loads, and a further chunk
 // costs it more than another tile costs the attention, up to pieces of seven
 // tiles (four where more than four row tiles make a tile dearer).  Calls with
 // few KV heads, whose pieces are the smallest, with a least piece of 3 tiles,

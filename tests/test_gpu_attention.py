@@ -158,8 +158,9 @@ def test_bf16_value_range(kind, v_scale):
 
 # The key pieces are planned on the device from ctx_lens: at 28/4 heads a
 # sequence of ctx keys is cut into about ceil((ctx / 64 + 1) / T) pieces with
-# T >= 4 tiles, so these contexts give one piece (no merge), two, a dozen and
-# several dozen (draft: 64 slots per KV head, verify: 32 per row group).
+# T >= 3 tiles (more where that would be more than 24 pieces), so these
+# contexts give one piece (no merge), two, a dozen and several dozen (draft:
+# 64 slots per KV head, verify: 32 per row group).
 @pytest.mark.parametrize("ctx", [100, 300, 3000, 20000])
 def test_piece_count_invariance(ctx):
     w = _w("verify_4k", batch=1)
@@ -190,8 +191,8 @@ def test_ring_lengths_one_piece_each(d):
 
 
 def test_workspace_reuse_across_shapes():
-    """One workspace serves calls of different shapes in turn: every call
-    leaves its arrival counters at zero for the next."""
+    """One workspace serves calls of different shapes in turn: nothing a call
+    reads from it was left by an earlier call."""
     w = _w("verify_4k", batch=2)
     ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
     for ctx, n, kind in (([3000, 1234], 64, "verify"), ([900, 20], 16, "draft"), ([5000, 4000], 64, "verify"),

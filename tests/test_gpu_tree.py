@@ -197,7 +197,7 @@ def test_clustered_slice_takes_the_exact_fallback(dtype):
     """Twenty of the row's best values in one 1024-value slice, five in each of
     its four 16-lane rows: the slice keeps only the values at or above the
     smallest row maximum (16 of them), so four of the row's best are left out
-    and the ranking pass must see that and select exactly from the whole row."""
+    and the ranking pass must see that and read the slice again."""
     g = torch.Generator().manual_seed(11)
     z = torch.randn(1, 3, 152064, generator=g)
     vpl = 8 if dtype == torch.bfloat16 else 4         # values per 16-byte load
