@@ -37,15 +37,15 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
 # Vector ALU issue peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3e12
-# full-rate lane operations per second (a 32x32 -> 64-bit multiply issues at
-# a quarter of that rate and counts as 4).
+# full-rate lane operations per second (a 64-bit multiply-add of 32-bit factors
+# is one of them, an exponential issues at half the rate and counts as 2).
 VALU_PEAK_TOPS = 39.32
 # Work of the sampling walk's row draws per token, in full-rate lane
 # operations: a quarter of what a group of four needs, one Philox4x32-10 call
-# (17 64-bit multiplies at 4 each, the first one an addition and two uniform,
-# plus 16 three-input XORs and that addition's 2: 86), the threshold on its
-# words and the test (12 and one exponential at 4) and the load and unpack (4).
-SAMPLE_OPS_PER_TOKEN = 26.5
+# (17 64-bit multiply-adds, the first one an addition and two uniform, plus 16
+# three-input XORs and that addition's 2: 35), the threshold on its words and
+# the test (12 and one exponential at 2) and the load and unpack (4).
+SAMPLE_OPS_PER_TOKEN = 13.25
 
 
 def parse():
