@@ -49,3 +49,31 @@ def test_workspace_and_outputs_follow_the_call_stream(monkeypatch):
     # a caller's workspace is used as given
     ws = ("tensor", "mine")
     assert G._workspace(10, "cuda:0", ws, stream="side") is ws
+
+
+def test_prepared_call_holds_marshalled_arguments():
+    """A prepared call converts its arguments once: every pointer, size and
+    number it passes is an object of the declared type (NULL pointers and the
+    shape reference stay as they are), with the value it was given."""
+    seen = []
+
+    class Fn:
+        argtypes = G._SIGS["glance_sample_accept"][1]
+
+        def __call__(self, *args):
+            seen.append(args)
+            return G.GLANCE_OK
+
+    values = [4, 64, 152064, G.GLANCE_BF16, 1 << 40, None, 1 << 41, 0.7, (1 << 64) - 1, (1 << 32) - 1, None, 3 << 40,
+              1 << 33, 1 << 34, 16, 1 << 35, 1 << 36, (1 << 40) + 5, 0]
+    fn = Fn()
+    assert len(values) == len(fn.argtypes)
+    call = G.PreparedCall(fn, values, None)
+    call()
+    call()
+    assert len(seen) == 2 and all(a is b for a, b in zip(*seen))
+    for t, v, a in zip(fn.argtypes, values, seen[0]):
+        if v is None:
+            assert a is None
+        else:
+            assert isinstance(a, t) and a.value == t(v).value
