@@ -120,7 +120,7 @@ def load_traffic(kernel_key, src, workload):
 COPY_BYTES = 256 << 20
 COPY_KERNEL = "neg_kernel"  # the calibration copy: out = -in over COPY_BYTES of fp32
 KERNEL_KEYS = {"draft": "attn_bf16<128, false", "verify": "attn_bf16<128, true",
-               "accept": "argmax_partial<true>", "tree_scan": "tree_scan<true>",
+               "accept": "argmax_partial<true, false>", "tree_scan": "tree_scan<true>",
                "tree_rank": "tree_rank<true>", "tree_enum": "tree_enum",
                "sample": "sample_partial<true>"}
 KERNEL_SRC = {"draft": "attn_bf16.hip", "verify": "attn_bf16.hip", "accept": "accept.hip",

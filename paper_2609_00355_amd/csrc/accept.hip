@@ -14,8 +14,14 @@
 // Rows of any vocabulary take the same vector loads: a row whose length is no
 // multiple of 16 bytes only makes them unaligned, which the memory pipeline
 // serves (at most one more cache line per wave-wide load); the values past a
-// row's last whole vector are loaded one by one.  2 x 33 x 50257 bf16, with
-// entropy: 13.6 us with one load per value, 7.6 us with these.
+// row's last whole vector are loaded one by one, beside the vectors.
+// 2 x 33 x 50257 bf16, with entropy: 13.6 us with one load per value, 7.6 us
+// with these.  Short chunks are latency and little else, so they take what
+// costs least of it: up to 256 values one a thread, bf16 chunks of up to 2048
+// one vector a thread with exact keys.  Graph-timed acceptances, with the long
+// chunks' eight loads and barrier and with these: 61 x 48 x 250 8.7 and 6.0
+// us, 61 x 48 x 1003 9.4 and 6.7, 4 x 64 x 1000 5.4 and 4.6, 200 x 64 x 2001
+// 30.9 and 17.7 (one load per value: 6.1, 6.9, 5.3 with vectors, 29.0).
 //
 // sample_partial  the sampling walk's row draws (temperature T > 0): the same
 //                 grid and packed reduction as argmax_partial over
@@ -232,12 +238,13 @@ __device__ __forceinline__ void entropy_chunk(const AcceptParams& p, int b, int 
         make_float4(M, (red_s[0] + red_s[1]) + (red_s[2] + red_s[3]), (red_t[0] + red_t[1]) + (red_t[2] + red_t[3]), 0.f);
 }
 
-template <bool BF16>
+// ENT: with the root entropy's workgroups, which come first, so that they end
+// with the others.
+template <bool BF16, bool ENT>
 __global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
   __shared__ unsigned long long red[4];
-  // the entropy's workgroups come first, so that they end with the others
-  const int ent_blocks = p.root_entropy ? p.batch * p.ent_chunks : 0;
-  if ((int)blockIdx.x < ent_blocks) {
+  const int ent_blocks = ENT ? p.batch * p.ent_chunks : 0;
+  if (ENT && (int)blockIdx.x < ent_blocks) {
     const int b = blockIdx.x / p.ent_chunks, c = blockIdx.x % p.ent_chunks;
     if (p.vocab <= 2048) entropy_chunk<BF16, 2048>(p, b, c);
     else entropy_chunk<BF16, kEntropyStep>(p, b, c);
@@ -249,18 +256,34 @@ __global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
   const int c0 = chunk * p.chunk_len;
   const int c1 = min(p.vocab, c0 + p.chunk_len);
   constexpr int V = BF16 ? 8 : 4;          // values per 16-byte load
-  const int cv = c0 + (c1 - c0) / V * V;   // end of the whole vectors
+  // end of the whole vectors (none in chunks of a value a thread at most)
+  const int cv = c1 - c0 <= 256 ? c0 : c0 + (c1 - c0) / V * V;
   const int tid = threadIdx.x;
   int best_key = (int)0x80000000;
   int best_idx = 0x7fffffff;
-  unsigned long long rest = 0ull;  // the values past them, one a thread
+  unsigned rest = 0u;  // a value past them, one a thread, used after the scan
   if (BF16) {
     const unsigned short* x = static_cast<const unsigned short*>(p.logits) + row * (long)p.vocab;
-    if (cv + tid < c1) rest = pack(order_key((unsigned int)x[cv + tid] << 16), cv + tid);
-    argmax_bf16_fast(x, c0, cv, tid, best_key, best_idx);
+    if (cv + tid < c1) rest = x[cv + tid];
+    if (c1 - c0 <= 256 * V) {
+      // a vector a thread at most: eight exact keys instead of the long
+      // chunks' eight loads and their barrier
+      const int e = c0 + V * tid;
+      if (e < cv) {
+        const u32x4 v = *reinterpret_cast<const u32x4_any*>(x + e);
+#pragma unroll
+        for (int w = 0; w < V; ++w) {
+          const int k = order_key(w & 1 ? v[w / 2] & 0xffff0000u : v[w / 2] << 16);
+          if (k > best_key) { best_key = k; best_idx = e + w; }
+        }
+      }
+    } else {
+      argmax_bf16_fast(x, c0, cv, tid, best_key, best_idx);
+    }
+    rest <<= 16;
   } else {
     const unsigned int* x = static_cast<const unsigned int*>(p.logits) + row * (long)p.vocab;
-    if (cv + tid < c1) rest = pack(order_key(x[cv + tid]), cv + tid);
+    if (cv + tid < c1) rest = x[cv + tid];
     constexpr int kUnroll = 4;
     for (int e0 = c0 + 4 * tid; e0 < cv; e0 += 4 * 256 * kUnroll) {
       u32x4 v[kUnroll];
@@ -283,7 +306,8 @@ __global__ __launch_bounds__(256) void argmax_partial(AcceptParams p) {
   }
   // threads that saw no element keep the smallest possible word
   unsigned long long w = (best_idx == 0x7fffffff) ? 0ull : pack(best_key, best_idx);
-  w = wave_max64(umax64(w, rest));
+  if (cv + tid < c1) w = umax64(w, pack(order_key(rest), cv + tid));
+  w = wave_max64(w);
   if ((tid & 63) == 0) red[tid >> 6] = w;
   __syncthreads();
   if (tid == 0) p.part[row * p.chunks + chunk] = umax64(umax64(red[0], red[1]), umax64(red[2], red[3]));
@@ -570,6 +594,7 @@ __global__ __launch_bounds__(256) void sample_partial(AcceptParams p) {
 // Lane v holds row v's token, its node's parent and the edge token, so a step
 // of the walk is a readlane and a ballot, with no memory access; lane k keeps
 // path entry k.
+template <bool ENT>
 __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
   const int b = blockIdx.x;
   const int lane = threadIdx.x;
@@ -580,9 +605,9 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
   int par = -1;
   int tok = 0;
   // the entropy's chunk statistics go out with the other loads (a lane's first)
-  const float4* ep = p.root_entropy ? p.ent_part + (long)b * p.ent_chunks : nullptr;
+  const float4* ep = ENT ? p.ent_part + (long)b * p.ent_chunks : nullptr;
   float4 e0 = {-__builtin_inff(), 0.f, 0.f, 0.f};
-  if (ep && lane < p.ent_chunks) e0 = ep[lane];
+  if (ENT && lane < p.ent_chunks) e0 = ep[lane];
   if (lane < n) {
     // the tree and the chunk words are all loaded before any is used (one
     // memory round trip; the argmax store below could alias the tree inputs,
@@ -628,7 +653,7 @@ __global__ __launch_bounds__(64) void accept_walk(AcceptParams p) {
     const unsigned r = __hip_atomic_load(p.round_counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(p.round_counter, r + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (ep) {
+  if (ENT) {
     // merge the chunks relative to the row maximum M
     float M = e0.x;
     for (int c = lane + 64; c < p.ent_chunks; c += 64) M = fmaxf(M, ep[c].x);
@@ -662,33 +687,33 @@ hipError_t launch_sample(const AcceptParams& p, bool bf16, hipStream_t s, hipEve
   hipError_t e = hipGetLastError();
   if (ev1) (void)hipEventRecord(ev1, s);
   if (e != hipSuccess) return e;
-  AcceptParams pw = p;
-  pw.root_entropy = nullptr;
-  hipLaunchKernelGGL(accept_walk, dim3(p.batch), dim3(64), 0, s, pw);
+  hipLaunchKernelGGL(accept_walk<false>, dim3(p.batch), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 
 hipError_t launch_accept(const AcceptParams& p, bool bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const long rows = (long)p.batch * p.n_nodes;
-  const long ent_blocks = p.root_entropy ? (long)p.batch * p.ent_chunks : 0;
-  auto launch = [&](const AcceptParams& q, long blocks) {
+  const bool ent = p.root_entropy != nullptr;
+  const long ent_blocks = ent ? (long)p.batch * p.ent_chunks : 0;
+  auto launch = [&](bool with_ent, long blocks) {
     const dim3 grid((unsigned)blocks), block(256);
-    if (bf16) hipLaunchKernelGGL(argmax_partial<true>, grid, block, 0, s, q);
-    else hipLaunchKernelGGL(argmax_partial<false>, grid, block, 0, s, q);
+    if (bf16 && with_ent) hipLaunchKernelGGL((argmax_partial<true, true>), grid, block, 0, s, p);
+    else if (bf16) hipLaunchKernelGGL((argmax_partial<true, false>), grid, block, 0, s, p);
+    else if (with_ent) hipLaunchKernelGGL((argmax_partial<false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((argmax_partial<false, false>), grid, block, 0, s, p);
   };
   if (ev0) (void)hipEventRecord(ev0, s);
   if (ent_blocks + rows * p.chunks < (1l << 24)) {
-    launch(p, ent_blocks + rows * p.chunks);
+    launch(ent, ent_blocks + rows * p.chunks);
   } else {  // a launch holds fewer than 2^32 threads: the entropy on its own
-    if (ent_blocks) launch(p, ent_blocks);
-    AcceptParams q = p;
-    q.root_entropy = nullptr;
-    launch(q, rows * p.chunks);
+    if (ent) launch(true, ent_blocks);
+    launch(false, rows * p.chunks);
   }
   hipError_t e = hipGetLastError();
   if (ev1) (void)hipEventRecord(ev1, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_walk, dim3(p.batch), dim3(64), 0, s, p);
+  if (ent) hipLaunchKernelGGL(accept_walk<true>, dim3(p.batch), dim3(64), 0, s, p);
+  else hipLaunchKernelGGL(accept_walk<false>, dim3(p.batch), dim3(64), 0, s, p);
   return hipGetLastError();
 }
 

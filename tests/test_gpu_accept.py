@@ -295,3 +295,38 @@ def test_root_entropy_with_lowest_finite_masks(dtype, batch, vocab, lo, hi):
     for b in range(batch):
         ref = OA.row_entropy(logits[b, 0])
         assert abs(h[b] - ref) <= 2e-4 + 2e-5 * abs(ref), (b, h[b], ref)
+
+
+# Chunks of up to 256 values take one value a thread, bf16 chunks of up to 2048
+# one exact vector a thread: both sides of both lines, with the values that an
+# order key has to get right at the first, last and odd places of a row.
+@pytest.mark.parametrize("vocab", [255, 256, 257, 264, 1003, 2047, 2048, 2049])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_short_rows(vocab, dtype):
+    g = torch.Generator().manual_seed(vocab)
+    x = torch.randn((2, 10, vocab), generator=g)
+    last, mid = vocab - 1, vocab // 2
+    x[:, 0, last] = 9.0
+    x[:, 1, 0] = x[:, 1, last] = 9.0        # a tie: 0
+    x[:, 2] = -1.0
+    x[:, 2, mid] = -0.0                     # -0 ties with the later +0
+    x[:, 2, last] = 0.0
+    x[:, 3, mid] = 50.0
+    x[:, 3, last] = -float("nan")           # a NaN of either sign is the largest
+    x[:, 4, mid + 1] = float("nan")
+    x[:, 4, last] = float("nan")            # the first one
+    x[:, 5] = -float("inf")                 # all equal: 0
+    x[:, 6, mid - 1] = x[:, 6, last] = float("inf")
+    x[:, 7] = torch.finfo(dtype).min
+    x[:, 7, last] = -3.0e38
+    x[:, 8] = -1.0
+    x[:, 8, 1] = 2e-40                      # subnormals in order
+    x[:, 8, last] = 3e-40
+    want = [last, 0, mid, last, mid + 1, 0, mid - 1, last, last]
+    logits = x.to(dtype)
+    par = torch.arange(-1, 9, dtype=torch.int32).repeat(2, 1)
+    tok = torch.tensor([[0] + want] * 2, dtype=torch.int32)
+    got = run_accept(logits, par, tok)
+    assert got["argmax"][:, :9].tolist() == [want] * 2
+    assert got["accept_len"].tolist() == [9, 9]
+    assert_accept_equal(got, logits, par, tok)
