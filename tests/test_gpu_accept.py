@@ -330,3 +330,22 @@ def test_short_rows(vocab, dtype):
     assert got["argmax"][:, :9].tolist() == [want] * 2
     assert got["accept_len"].tolist() == [9, 9]
     assert_accept_equal(got, logits, par, tok)
+
+
+def test_entropy_beyond_one_launch():
+    """2^24 - 64 rows and 262143 entropy workgroups: together more threads than
+    one launch holds (2^32), so the entropy goes out on its own."""
+    batch, n, vocab = 262143, 64, 3
+    g = torch.Generator(device="cuda").manual_seed(3)
+    logits = torch.randn((batch, n, vocab), generator=g, device="cuda")
+    par = torch.arange(-1, n - 1, dtype=torch.int32, device="cuda").repeat(batch, 1)
+    am = logits.argmax(-1).to(torch.int32)
+    tok = torch.cat([torch.zeros((batch, 1), dtype=torch.int32, device="cuda"), am[:, :-1]], 1).contiguous()
+    tok[:, 5] += 3                                   # the walk of the chain ends at node 4
+    res = G.glance_greedy_accept(logits, par, tok, path_stride=8, want_entropy=True)
+    assert torch.equal(res["argmax"], am)
+    assert bool((res["accept_len"] == 4).all()) and torch.equal(res["next_root"], am[:, 4])
+    assert torch.equal(res["accept_path"], torch.tensor([0, 1, 2, 3, 4, -1, -1, -1], dtype=torch.int32, device="cuda").repeat(batch, 1))
+    p = torch.log_softmax(logits[:, 0].double(), -1)
+    h = -(p.exp() * p).sum(-1)
+    assert float((res["root_entropy"].double() - h).abs().max()) <= 2e-4
